@@ -28,6 +28,8 @@
 
 #include "analytic.hpp"
 #include "common.hpp"
+#include "f64_mfma.hpp"
+#include "f64_tile.hpp"
 #include "modular.hpp"
 #include "mlp_mfma.hpp"
 #include "mlp_mfma_tile.hpp"
@@ -64,6 +66,7 @@ struct Mod {
   Ctrl ctrl;
   R* ckpt;          // [B, ck_cap, D] y_n for n = 0, k, 2k, ... (or nullptr)
   int32_t ck_every, ck_cap;
+  R *wp, *wpT;      // FP64 matrix cores: packed layers, transposed layers
 };
 
 // Stage input Y = y + hs * sum_j coef_j K[kidx_j]; field time t + c hs.
@@ -127,7 +130,7 @@ struct Back {
   // segment's recomputation runs on a second stream while this segment's
   // vector-Jacobian products run, with its own step view act2, bh2, bt2.
   R* Yst;
-  float* Ast;
+  R* Ast;
   size_t yst_half, ast_half;
   int32_t* act2;
   R* bh2;
@@ -164,7 +167,7 @@ inline long n_params(int din, int H) {
   return n0 * H + H + (long)H * H + H + (long)H * din + din;
 }
 
-// ---- field kernel (FMA path: FP64 validation mode and FP32 mode) -------------
+// ---- field kernel (FMA path: shapes the matrix-core kernels are not built for)
 //
 // ROWS instances per workgroup; thread j owns output column j of every layer
 // for those rows (coalesced weight reads, broadcast activation reads from
@@ -838,6 +841,78 @@ hipError_t fused_launch(const Mod<float>& m, const FusedArgs& f, int f32,
                : fused_h<mtile::Bf3, false, M>(m, f, s);
 }
 
+// FP64: the same whole-solve launch on the FP64 matrix cores (f64_tile.hpp),
+// a tile of 4 to 16 instances per workgroup of eight wavefronts; the rows'
+// commits are one wavefront each.
+struct Fused64Args {
+  F64Args st[6];
+  int budget, kl_off;
+};
+
+template <int MT, int NT, bool CNF, class M, bool KL>
+__global__ __launch_bounds__(64 * f64t::kWV) void solve_fused64_kernel(
+    Mod<double> m, Fused64Args f) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  constexpr int PR = CNF ? 2 * MT : 4 * MT;
+  const int r0 = blockIdx.x * PR;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int D = m.D;
+  double* smem = reinterpret_cast<double*>(smem_raw);
+  double* kl = KL ? reinterpret_cast<double*>(smem_raw + f.kl_off) : nullptr;
+  if (KL)
+    for (int i = threadIdx.x; i < PR * D; i += blockDim.x) {
+      const int row = r0 + i / D;
+      kl[i] = row < m.B ? m.K[(long)row * D + i % D] : 0.0;
+    }
+  __shared__ int active;
+  for (int round = 0; round < f.budget; ++round) {
+    __syncthreads();
+    if (threadIdx.x == 0) active = 0;
+    __syncthreads();
+    if (threadIdx.x < PR && r0 + (int)threadIdx.x < m.B &&
+        m.st.status[r0 + threadIdx.x] == kRunning)
+      active = 1;
+    __syncthreads();
+    if (!active) break;
+    for (int s = 0; s < 6; ++s) {
+      f64t::field_tile<MT, NT, CNF, KL>(f.st[s], r0, smem, kl);
+      __syncthreads();
+    }
+    for (int r = wave; r < PR; r += f64t::kWV)
+      commit_row<double, M, false, 64, KL>(m, r0 + r, lane,
+                                           KView<double>{kl, PR * D, r});
+  }
+  if (KL) {  // the FSAL stage back to HBM
+    __syncthreads();
+    for (int i = threadIdx.x; i < PR * D; i += blockDim.x) {
+      const int row = r0 + i / D;
+      if (row < m.B) m.K[(long)row * D + i % D] = kl[i];
+    }
+  }
+}
+
+template <class M>
+hipError_t fused64_launch(const Mod<double>& m, Fused64Args f,
+                          hipStream_t s) {
+  return f64t::with_shape(
+      m.B, m.d_in, m.H, m.cnf, [&](auto mt, auto nt, auto cnf) {
+        constexpr int MT = mt(), NT = nt(), PR = cnf() ? 2 * MT : 4 * MT;
+        constexpr bool CNF = cnf();
+        size_t sm = sizeof(double) * f64t::lds_elems(4 * MT, m.d_in, m.H);
+        f.kl_off = (int)sm;
+        const size_t smk = sm + sizeof(double) * 7 * PR * (size_t)m.D;
+        const bool kl = smk <= f64t::kLdsMax;
+        if (kl) sm = smk;
+        auto k = kl ? solve_fused64_kernel<MT, NT, CNF, M, true>
+                    : solve_fused64_kernel<MT, NT, CNF, M, false>;
+        const hipError_t e = f64t::allow_lds(k, sm);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k, dim3((m.B + PR - 1) / PR), dim3(64 * f64t::kWV),
+                           sm, s, m, f);
+        return hipGetLastError();
+      });
+}
+
 __global__ void count_equal_kernel(const int32_t* a, int n, int32_t v,
                                    int32_t* out) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -916,8 +991,15 @@ struct Lay {
   }
 };
 
+// FP64 runs on the FP64 matrix cores while a tile's layers fit in LDS (else
+// the FMA kernels).
+inline bool uses_f64(const bode_config& c, int din) {
+  return c.precision == BODE_FP64 &&
+         f64_fits(c.D, din, c.mlp_hidden, c.rhs == BODE_RHS_CNF);
+}
+
 // BF16 always runs on the matrix cores; FP32 does where the shape is built
-// (else the FMA kernels); FP64 uses the FMA kernels.
+// (else the FMA kernels).
 inline bool uses_mfma(const bode_config& c, int din) {
   if (c.precision == BODE_BF16) return true;
   return c.precision == BODE_FP32 && mfma_supported(din, c.mlp_hidden).empty();
@@ -997,13 +1079,13 @@ size_t lay_mod(const bode_config& c, void* base, Mod<R>* m, MfmaWeights* mw,
     bk.T3in = L.take<R>((size_t)(H + 1) * bk.K);
     bk.T3g = L.take<R>((size_t)din * bk.K);
     const size_t Bs = B * (c.rhs == BODE_RHS_CNF ? 2 : 1);
-    const size_t store = (size_t)k * 7 * (B * D * sizeof(R) + Bs * 2 * H * 4);
-    if (std::is_same<R, float>::value && uses_mfma(c, din) &&
+    const size_t store = (size_t)k * 7 * (B * D + Bs * 2 * H) * sizeof(R);
+    if ((uses_mfma(c, din) || uses_f64(c, din)) &&
         store <= (size_t(2) << 30)) {
       bk.yst_half = (size_t)k * 7 * B * D;
       bk.ast_half = (size_t)k * 7 * Bs * 2 * H;
       bk.Yst = L.take<R>(2 * bk.yst_half);
-      bk.Ast = L.take<float>(2 * bk.ast_half);
+      bk.Ast = L.take<R>(2 * bk.ast_half);
       bk.act2 = L.take<int32_t>(B);
       bk.bh2 = L.take<R>(B);
       bk.bt2 = L.take<double>(B);
@@ -1019,8 +1101,15 @@ size_t lay_mod(const bode_config& c, void* base, Mod<R>* m, MfmaWeights* mw,
     w.packedT =
         L.take<unsigned char>(mfma_packedT_bytes(din, c.mlp_hidden, w.f32));
   }
+  R *wp = nullptr, *wpT = nullptr;
+  if (uses_f64(c, din)) {
+    wp = L.take<R>(f64_packed_elems(din, c.mlp_hidden));
+    wpT = L.take<R>(f64_packedT_elems(din, c.mlp_hidden));
+  }
   if (m) {
     m->st = st;
+    m->wp = wp;
+    m->wpT = wpT;
     m->K = K;
     m->Y7 = Y7;
     m->hs = hs;
@@ -1073,10 +1162,44 @@ template <typename R>
 hipError_t field(ModImpl& im, const Mod<R>& m, const StageSpec& sp, R* out,
                  hipStream_t s);
 
+F64Args f64_args(const Mod<double>& m, const StageSpec& sp, double* out) {
+  F64Args a{};
+  a.B = m.B;
+  a.D = m.D;
+  a.din = m.d_in;
+  a.H = m.H;
+  a.cnf = m.cnf;
+  a.status = m.st.status;
+  a.y = m.st.y;
+  a.K = m.K;
+  a.hs = m.hs;
+  a.t = m.st.t;
+  a.eps = m.eps;
+  a.W = m.wp;
+  a.b1 = m.b1;
+  a.b2 = m.b2;
+  a.b3 = m.b3;
+  a.n = sp.n;
+  for (int j = 0; j < 6; ++j) {
+    a.kidx[j] = sp.kidx[j];
+    a.coef[j] = sp.coef[j];
+  }
+  a.c = sp.c;
+  a.write_y7 = sp.yout != nullptr;
+  a.Y7 = static_cast<double*>(sp.yout);
+  a.out = out;
+  a.act_out = static_cast<double*>(sp.act_out);
+  return a;
+}
+
 template <>
 hipError_t field<double>(ModImpl&, const Mod<double>& m, const StageSpec& sp,
                          double* out, hipStream_t s) {
-  return launch_field_fma<double>(m, sp, out, s);
+  if (m.wp == nullptr) return launch_field_fma<double>(m, sp, out, s);
+  F64Steps v{};
+  v.n = 1;
+  v.st[0] = f64_args(m, sp, out);
+  return launch_field_f64(v, s);
 }
 
 MfmaArgs stage_args(const ModImpl& im, const Mod<float>& m,
@@ -1119,6 +1242,19 @@ hipError_t run_fused(const ModImpl& im, const Mod<float>& m, int budget,
   }
   f.budget = budget;
   return fused_launch<M>(m, f, im.mw.f32, im.mw.plain, s);
+}
+
+template <class M>
+hipError_t run_fused64(const Mod<double>& m, int budget, hipStream_t s) {
+  Fused64Args f{};
+  for (int st = 1; st < 7; ++st) {
+    StageSpec sp = stage_spec<M>(st);
+    if (st == 6) sp.yout = m.Y7;
+    f.st[st - 1] = f64_args(m, sp, m.K + (size_t)st * m.B * m.D);
+    f.st[st - 1].kslot = st;
+  }
+  f.budget = budget;
+  return fused64_launch<M>(m, f, s);
 }
 
 template <typename R>
@@ -1197,6 +1333,9 @@ hipError_t run_rounds(ModImpl& im, Mod<R>& m, int budget, hipStream_t s) {
     if (im.mw.packed != nullptr && !m.keep)
       return im.cfg.method == BODE_TSIT5 ? run_fused<Tsit5>(im, m, budget, s)
                                          : run_fused<Dopri5>(im, m, budget, s);
+  } else if (m.wp != nullptr && !m.keep) {
+    return im.cfg.method == BODE_TSIT5 ? run_fused64<Tsit5>(m, budget, s)
+                                       : run_fused64<Dopri5>(m, budget, s);
   }
   auto rounds = [&](int n, hipStream_t q) -> hipError_t {
     for (int r = 0; r < n; ++r) {
@@ -1336,6 +1475,11 @@ hipError_t modular_init(ModularPlan& mp, const bode_config& c,
   if (im->is64) {
     fill_mod<double>(&im->md, c, p);
     publish(im->md);
+    if (im->md.wp != nullptr) {
+      e = f64_pack_weights(im->md.wp, im->md.wpT, im->md.d_in, c.mlp_hidden,
+                           im->md.W1, im->md.W2, im->md.W3, s);
+      if (e != hipSuccess) return e;
+    }
     return init_launch<double>(*im, im->md, s);
   }
   fill_mod<float>(&im->mf, c, p);
@@ -1385,7 +1529,7 @@ struct VjpSpec {
   // Matrix-core fields with the segment store: the stage input and the
   // stored hidden-layer values of this stage (null: Ys and recomputation).
   const void* Y;
-  const float* act_in;
+  const void* act_in;
 };
 
 template <typename R>
@@ -1730,7 +1874,7 @@ MfmaVjpArgs vjp_args(const ModImpl& im, const Mod<float>& m,
   a.act = b.act;
   a.Y = sp.Y != nullptr ? static_cast<const float*>(sp.Y)
                         : b.Ys + (long)(sp.s - 1) * m.B * m.D;
-  a.act_in = sp.act_in;
+  a.act_in = static_cast<const float*>(sp.act_in);
   a.kap_s = b.kap + (long)(sp.s - 1) * m.B * m.D;
   a.eps = m.eps;
   a.bh = b.bh;
@@ -1758,6 +1902,45 @@ MfmaVjpArgs vjp_args(const ModImpl& im, const Mod<float>& m,
   return a;
 }
 
+// The FP64 matrix-core VJP's arguments.
+F64VjpArgs vjp_args64(const Mod<double>& m, const Back<double>& b,
+                      const VjpSpec& sp) {
+  F64VjpArgs a{};
+  a.B = m.B;
+  a.D = m.D;
+  a.din = m.d_in;
+  a.H = m.H;
+  a.cnf = m.cnf;
+  a.act = b.act;
+  a.Y = sp.Y != nullptr ? static_cast<const double*>(sp.Y)
+                        : b.Ys + (long)(sp.s - 1) * m.B * m.D;
+  a.act_in = static_cast<const double*>(sp.act_in);
+  a.kap_s = b.kap + (long)(sp.s - 1) * m.B * m.D;
+  a.eps = m.eps;
+  a.bh = b.bh;
+  a.bt = b.bt;
+  a.c = sp.c;
+  a.WT = m.wpT;
+  a.T1in = b.T1in;
+  a.T1g = b.T1g;
+  a.T2in = b.T2in;
+  a.T2g = b.T2g;
+  a.T3in = b.T3in;
+  a.T3g = b.T3g;
+  a.kb = sp.kbase + (long)(sp.s - 1) * (m.cnf ? 2L * m.B : (long)m.B);
+  a.s = sp.s;
+  a.n = sp.n;
+  for (int j = 0; j < sp.n; ++j) {
+    a.kidx[j] = sp.kidx[j];
+    a.coef[j] = sp.coef[j];
+  }
+  a.lam = b.lam;
+  a.lamn = b.lamn;
+  a.kap = b.kap;
+  a.mu_out = static_cast<double*>(sp.mu_out);
+  return a;
+}
+
 // Matrix-core modes: the stage's VJP on MFMA (BF16: BF16 weights, three-way
 // split activations and cotangents; FP32: FP32 operands; both accumulate in
 // FP32); else the FMA kernel.
@@ -1767,6 +1950,11 @@ hipError_t vjp(const ModImpl& im, const Mod<R>& m, const Back<R>& b,
   if constexpr (std::is_same<R, float>::value) {
     if (im.mw.packedT != nullptr)
       return launch_vjp_mfma(vjp_args(im, m, b, sp), s);
+  } else if (m.wpT != nullptr && sp.act_in != nullptr) {
+    F64VjpSteps v{};
+    v.n = 1;
+    v.st[0] = vjp_args64(m, b, sp);
+    return launch_vjp_f64(v, s);
   }
   return launch_vjp<R>(m, b, sp, s);
 }
@@ -2416,6 +2604,7 @@ hipError_t stages_store(ModImpl& im, Mod<R> v, Back<R>& b, int j,
   const size_t AH = (size_t)v.B * (v.cnf ? 2 : 1) * 2 * v.H;
   hipError_t e = hipSuccess;
   [[maybe_unused]] MfmaSteps fs{};
+  [[maybe_unused]] F64Steps f64{};
   for (int st = 0; st < 7 && e == hipSuccess; ++st) {
     StageSpec sp = st == 0 ? StageSpec{} : stage_spec<M>(st);
     sp.yout = st == 0 ? nullptr : b.Yst + ((size_t)j * 7 + st) * BD;
@@ -2427,11 +2616,18 @@ hipError_t stages_store(ModImpl& im, Mod<R> v, Back<R>& b, int j,
         fs.kl = 1;  // the stage values are read only by the later stages
         continue;
       }
+    } else if (v.wp != nullptr) {
+      f64.st[f64.n] = f64_args(v, sp, b.Ks + (size_t)st * BD);
+      f64.st[f64.n++].kslot = st;
+      f64.kl = 1;
+      continue;
     }
     e = field<R>(im, v, sp, b.Ks + (size_t)st * BD, s);
   }
   if constexpr (std::is_same<R, float>::value) {
     if (e == hipSuccess && fs.n > 0) e = launch_field_steps_mfma(fs, s);
+  } else if (e == hipSuccess && f64.n > 0) {
+    e = launch_field_f64(f64, s);
   }
   return e;
 }
@@ -2441,7 +2637,15 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
                       const R* g_final, R* dy0, R* dtheta, hipStream_t s) {
   const long BD = (long)m.B * m.D;
   const dim3 rows_g((m.B + 3) / 4), blk(256);
-  if (im.mw.packedT == nullptr) {
+  // the FP64 adjoint is offered for the widths the FMA kernel's LDS holds
+  if (m.wpT != nullptr && vjp_smem<R>(1, m.d_in + 1, m.D, m.H, m.d_in,
+                                      m.cnf) > 65536)
+    return hipErrorInvalidValue;
+  // VJPs on the matrix cores (FP64: only on stored layers)
+  const bool mat = std::is_same<R, float>::value
+                       ? im.mw.packedT != nullptr
+                       : m.wpT != nullptr && b.Yst != nullptr;
+  if (!mat) {
     // tape inputs of tiles no step writes must be finite (they meet 0); the
     // matrix-core VJP kernels write zeros into those rows themselves
     const long n1 = (long)(m.d_in + 2) * b.K, n2 = (long)(m.H + 1) * b.K;
@@ -2474,7 +2678,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
   // chunk's GEMMs run on a third stream while the next chunk's VJPs write
   // the other half; a half is rewritten only after its GEMMs are done.
   // Every GEMM adds into the slots on that one stream, in chunk order.
-  const bool ovl = im.mw.packedT != nullptr && b.C >= 2 && nmax > 1;
+  const bool ovl = mat && b.C >= 2 && nmax > 1;
   const int Cc = ovl ? b.C / 2 : b.C;
   // k-split slots: a GEMM over K tape rows uses at most K / 256 of them, so
   // only those of the largest chunk are cleared and summed
@@ -2491,7 +2695,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
     if (e == hipSuccess) e = shared_aux_stream2(&s3);
     if (e != hipSuccess) return e;
   }
-  auto back_step = [&](int n, const R* Yh, const float* Ah, int j,
+  auto back_step = [&](int n, const R* Yh, const R* Ah, int j,
                        int setup) -> hipError_t {
     // this step's place in its tape chunk (steps are taken in reverse)
     const int idx = nmax - 1 - n, chunk = idx / Cc, slot_c = idx % Cc;
@@ -2506,13 +2710,15 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
     // the seven stages in one launch on the matrix cores while the batch
     // has few tiles (launches, not the tiles' work, set its pace; the
     // dense-output part then runs in the same launch), else one launch
-    // each (a CNF step of 8192 instances: 16.9 ms one each, 18.9 in one)
-    [[maybe_unused]] MfmaVjpSteps vs{};
-    const bool steps = std::is_same<R, float>::value && im.mw.packedT &&
-                       few_tiles(m);
+    // each (a CNF step of 8192 instances: 16.9 ms one each, 18.9 in one);
+    // FP64 always takes the one launch
+    typename std::conditional<std::is_same<R, float>::value, MfmaVjpSteps,
+                              F64VjpSteps>::type vs{};
+    const bool steps =
+        mat && (!std::is_same<R, float>::value || few_tiles(m));
     if (steps) {
-      if constexpr (std::is_same<R, float>::value) {
-        VjpDense& d = vs.dense;
+      {
+        VjpDenseT<R>& d = vs.dense;
         d.on = 1;
         d.setup = setup;
         d.step = n;
@@ -2525,7 +2731,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
         d.t_eval = m.t_eval;
         d.g_eval = g_eval;
         for (int jj = 0; jj < 7; ++jj)
-          for (int q = 0; q < 4; ++q) d.P[jj][q] = float(M::P[jj][q]);
+          for (int q = 0; q < 4; ++q) d.P[jj][q] = R(M::P[jj][q]);
         d.act = b.act;
         d.bh = b.bh;
         d.bt = b.bt;
@@ -2534,7 +2740,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
       hipLaunchKernelGGL((adj_dense<R, M>), rows_g, blk, 0, s, m, b, n,
                          g_eval, setup);
     }
-    if (im.mw.packedT == nullptr) {
+    if (!mat) {
       // FMA kernels skip tiles without a step n: their cotangent rows must
       // read as zero (the matrix-core kernels write those zeros themselves)
       const long H = m.H, rows = 7 * Bs;
@@ -2562,17 +2768,22 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
         sp.kidx[q] = ss.kidx[q];
         sp.coef[q] = ss.coef[q];
       }
-      if constexpr (std::is_same<R, float>::value) {
-        if (steps) {
+      if (steps) {
+        if constexpr (std::is_same<R, float>::value)
           vs.st[vs.n++] = vjp_args(im, m, b, sp);
-          continue;
-        }
+        else
+          vs.st[vs.n++] = vjp_args64(m, b, sp);
+        continue;
       }
       const hipError_t r = vjp<R>(im, m, b, sp, s);
       if (r != hipSuccess) return r;
     }
     if (steps) {
-      const hipError_t r = launch_vjp_steps_mfma(vs, s);
+      hipError_t r;
+      if constexpr (std::is_same<R, float>::value)
+        r = launch_vjp_steps_mfma(vs, s);
+      else
+        r = launch_vjp_f64(vs, s);
       if (r != hipSuccess) return r;
     }
     if (slot_c == Cc - 1 || n == 0) {
@@ -2665,7 +2876,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
       if (q > 0) e = recompute(q - 1);  // enqueued ahead of q's chain
       if (e == hipSuccess) e = hipStreamWaitEvent(s, ready[q & 1], 0);
       const R* Yh = b.Yst + (q & 1) * b.yst_half;
-      const float* Ah = b.Ast + (q & 1) * b.ast_half;
+      const R* Ah = b.Ast + (q & 1) * b.ast_half;
       for (int n = seg_top(q); n >= q * k && e == hipSuccess; --n)
         e = back_step(n, Yh, Ah, n - q * k, 1);
       if (e == hipSuccess) e = hipEventRecord(freed[q & 1], s);
