@@ -844,13 +844,11 @@ hipError_t launch_vjp_steps_mfma(const MfmaVjpSteps& v, hipStream_t s) {
   return vjp_any(v.st[0], &v, s);
 }
 
+// (FP32 only: BF16 mode's forward kernels are neural_fwd.inc's)
 static hipError_t field_any(const MfmaArgs& a, const MfmaSteps* v,
                             hipStream_t s) {
-  if (a.w.f32)
-    return a.cnf ? field_h<F32, true>(a, v, s) : field_h<F32, false>(a, v, s);
-  if (a.w.plain)
-    return a.cnf ? field_h<Bf1, true>(a, v, s) : field_h<Bf1, false>(a, v, s);
-  return a.cnf ? field_h<Bf3, true>(a, v, s) : field_h<Bf3, false>(a, v, s);
+  if (!a.w.f32) return hipErrorInvalidValue;
+  return a.cnf ? field_h<F32, true>(a, v, s) : field_h<F32, false>(a, v, s);
 }
 
 hipError_t launch_field_mfma(const MfmaArgs& a, int row_tile, hipStream_t s) {

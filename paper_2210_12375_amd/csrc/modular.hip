@@ -30,9 +30,11 @@
 #include "common.hpp"
 #include "f64_mfma.hpp"
 #include "f64_tile.hpp"
+#include "mod.hpp"
 #include "modular.hpp"
 #include "mlp_mfma.hpp"
 #include "mlp_mfma_tile.hpp"
+#include "neural_fwd.hpp"
 #include "tableau.hpp"
 
 namespace bode {
@@ -40,34 +42,6 @@ namespace bode {
 namespace {
 constexpr int kRoundsPerSync = 8;
 }
-
-// ---- device-side description ------------------------------------------------
-
-template <typename R>
-struct Mod {
-  int32_t B, D, E, H, cnf, d_in;  // d_in: state features fed to the field
-  const R* y0;
-  const double *t0, *t_end, *rtol, *atol, *t_eval, *h0;
-  const R *W1, *b1, *W2, *b2, *W3, *b3, *eps;
-  R* y_eval;
-  R* y_final;
-  State<R> st;     // t, h, error history, counters, status, cursor, y, k1
-  R* K;            // [7, B, D] stages (K[0] = k1 = st.k1)
-  R* Y7;           // [B, D] stage-7 input = candidate solution
-  R* hs;           // [B] size of the current attempt
-  int32_t* last;   // [B] the current attempt ends on t_end
-  R* aux;          // [B] start-step scratch
-  double* h_rec;   // [B, rec_cap] attempt record (rejected < 0)
-  double* e_rec;   // [B, rec_cap] the attempts' error norms
-  int32_t rec_cap;
-  int32_t* n_running;
-  DenseKeep<R> dk;
-  int32_t keep;
-  Ctrl ctrl;
-  R* ckpt;          // [B, ck_cap, D] y_n for n = 0, k, 2k, ... (or nullptr)
-  int32_t ck_every, ck_cap;
-  R *wp, *wpT;      // FP64 matrix cores: packed layers, transposed layers
-};
 
 // Stage input Y = y + hs * sum_j coef_j K[kidx_j]; field time t + c hs.
 struct StageSpec {
@@ -829,16 +803,10 @@ hipError_t fused_h(const Mod<float>& m, const FusedArgs& f, hipStream_t s) {
 }
 
 template <class M>
-hipError_t fused_launch(const Mod<float>& m, const FusedArgs& f, int f32,
-                        int plain, hipStream_t s) {
-  if (f32)
-    return m.cnf ? fused_h<mtile::F32, true, M>(m, f, s)
-                 : fused_h<mtile::F32, false, M>(m, f, s);
-  if (plain)
-    return m.cnf ? fused_h<mtile::Bf1, true, M>(m, f, s)
-                 : fused_h<mtile::Bf1, false, M>(m, f, s);
-  return m.cnf ? fused_h<mtile::Bf3, true, M>(m, f, s)
-               : fused_h<mtile::Bf3, false, M>(m, f, s);
+hipError_t fused_launch(const Mod<float>& m, const FusedArgs& f,
+                        hipStream_t s) {
+  return m.cnf ? fused_h<mtile::F32, true, M>(m, f, s)
+               : fused_h<mtile::F32, false, M>(m, f, s);
 }
 
 // FP64: the same whole-solve launch on the FP64 matrix cores (f64_tile.hpp),
@@ -1223,6 +1191,8 @@ MfmaArgs stage_args(const ModImpl& im, const Mod<float>& m,
 template <>
 hipError_t field<float>(ModImpl& im, const Mod<float>& m, const StageSpec& sp,
                         float* out, hipStream_t s) {
+  if (im.mw.packed != nullptr && !im.mw.f32)
+    return fwd_stage(stage_args(im, m, sp, out), s);
   if (im.mw.packed != nullptr)
     return launch_field_mfma(stage_args(im, m, sp, out), 0, s);
   return launch_field_fma<float>(m, sp, out, s);
@@ -1233,6 +1203,9 @@ hipError_t field<float>(ModImpl& im, const Mod<float>& m, const StageSpec& sp,
 template <class M>
 hipError_t run_fused(const ModImpl& im, const Mod<float>& m, int budget,
                      hipStream_t s) {
+  if (!im.mw.f32)
+    return fwd_solve(m, im.mw, tableau_args<M>(), budget,
+                     get_tune(im.cfg).waves, s);
   FusedArgs f{};
   for (int st = 1; st < 7; ++st) {
     StageSpec sp = stage_spec<M>(st);
@@ -1241,7 +1214,7 @@ hipError_t run_fused(const ModImpl& im, const Mod<float>& m, int budget,
     f.st[st - 1].kslot = st;
   }
   f.budget = budget;
-  return fused_launch<M>(m, f, im.mw.f32, im.mw.plain, s);
+  return fused_launch<M>(m, f, s);
 }
 
 template <class M>
@@ -2605,6 +2578,24 @@ hipError_t stages_store(ModImpl& im, Mod<R> v, Back<R>& b, int j,
   hipError_t e = hipSuccess;
   [[maybe_unused]] MfmaSteps fs{};
   [[maybe_unused]] F64Steps f64{};
+  if constexpr (std::is_same<R, float>::value) {
+    if (im.mw.packed != nullptr && !im.mw.f32) {  // the seven in one launch
+      FwdSteps f{};
+      f.B = v.B;
+      f.D = v.D;
+      f.status = v.st.status;
+      f.y = v.st.y;
+      f.hs = v.hs;
+      f.eps = v.eps;
+      f.t = v.st.t;
+      for (int st = 0; st < 7; ++st) {
+        f.Y[st] = st == 0 ? nullptr : b.Yst + ((size_t)j * 7 + st) * BD;
+        f.act[st] = b.Ast + ((size_t)j * 7 + st) * AH;
+      }
+      return fwd_steps(f, v.d_in, v.H, v.cnf, im.mw, tableau_args<M>(),
+                       get_tune(im.cfg).waves, s);
+    }
+  }
   for (int st = 0; st < 7 && e == hipSuccess; ++st) {
     StageSpec sp = st == 0 ? StageSpec{} : stage_spec<M>(st);
     sp.yout = st == 0 ? nullptr : b.Yst + ((size_t)j * 7 + st) * BD;

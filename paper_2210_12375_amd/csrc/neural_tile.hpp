@@ -1,0 +1,541 @@
+// The neural field of one row tile on the matrix cores of gfx950, with the
+// stage arithmetic around it held in registers: the building block of the
+// forward kernels (neural_fwd.inc).
+//
+// A workgroup owns RT = 16 MT rows (MLP: instances; CNF: instances and their
+// tangent rows, 8 + 8 in one 16-row tile or, MT = 2, a tile of each).  The
+// products run transposed, C^T = W^T A^T: the weights are the 16-row operand
+// and the instances the 16 columns of v_mfma_f32_16x16x32_bf16, so a lane
+// ends up with four consecutive features of one instance (instance l % 16,
+// features 4 (l / 16) .. + 3 of a 16-feature tile).  Activations are split
+// into BF16 terms and stored to LDS four at a time (one 8-byte store per
+// term), and the state-sized vectors (y, the seven stages, the probe) stay
+// in the registers of the lanes that own those elements for a whole solve:
+// forming a stage input, the error estimate and the dense output touches no
+// memory.
+//
+// Weights are the same packed 16x32 fragments as the adjoint kernels'.
+// RES: all three layers stay in registers for the whole launch (width 256
+// and up to 64 state features in BF16: 24 fragments, 96 registers in each of
+// 8 wavefronts), so no evaluation reads a weight; otherwise they stream from
+// L2 through a ring of k blocks requested one phase ahead.
+// Measured against a field kernel that read its weights from L2 and its
+// stages from LDS for every evaluation: solve of 4096 instances of
+// 65->256->256->64 309 -> 177 us, of the 8192-instance CNF 17->512->512->16
+// 2.55 -> 1.33 ms.
+// The output layer's k blocks are split over the wavefronts its few feature
+// tiles would leave idle (partials meet in LDS, summed in a fixed order).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "common.hpp"
+#include "mlp_mfma.hpp"
+#include "mlp_mfma_tile.hpp"
+
+namespace bode {
+namespace ntile {
+
+using mtile::fast_tanh;
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// Operand policies: BF16 terms per activation and per weight, and the
+// products issued (weight term, activation term), smallest first.
+struct Bf3 {
+  static constexpr int kA = 3, kW = 1, kN = 3;
+  static constexpr int kTerm[kN][2] = {{0, 2}, {0, 1}, {0, 0}};
+};
+struct Bf1 {
+  static constexpr int kA = 1, kW = 1, kN = 1;
+  static constexpr int kTerm[kN][2] = {{0, 0}};
+};
+
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(
+                                          f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float lo_f(uint32_t u) {
+  return __uint_as_float(u << 16);
+}
+__device__ __forceinline__ float hi_f(uint32_t u) {
+  return __uint_as_float(u & 0xffff0000u);
+}
+
+// Four values as BF16 terms (rounded to nearest; each residual is exact, so
+// three terms sum to the value), one 8-byte store per term.  SAFE: values
+// beyond 2^127 (whose rounding could overflow) keep their top 16 bits.
+template <int kA, bool SAFE>
+__device__ __forceinline__ void put4(uint16_t* p, int plane, f32x4 v) {
+  // (the residuals are of the rounded value: no fusing with its product)
+#pragma clang fp contract(off)
+  f32x4 h = v;
+  if (SAFE) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (!(fabsf(v[i]) < 1.7014118e38f))
+        h[i] = __uint_as_float(__float_as_uint(v[i]) & 0xffff0000u);
+  }
+  uint32_t a = pack2(h[0], h[1]), b = pack2(h[2], h[3]);
+  *reinterpret_cast<u32x2*>(p) = u32x2{a, b};
+#pragma unroll
+  for (int k = 1; k < kA; ++k) {
+    v[0] -= lo_f(a);
+    v[1] -= hi_f(a);
+    v[2] -= lo_f(b);
+    v[3] -= hi_f(b);
+    a = pack2(v[0], v[1]);
+    b = pack2(v[2], v[3]);
+    *reinterpret_cast<u32x2*>(p + k * plane) = u32x2{a, b};
+  }
+}
+
+// The value of the lane 8 places away within its row of 16 lanes.
+__device__ __forceinline__ float xor8(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(
+      0, __float_as_uint(v), 0x128, 0xf, 0xf, true));  // row_ror:8
+}
+
+// Shape constants.  NTW feature tiles of the hidden layers per wavefront,
+// NO output tiles per wavefront.
+template <class Op_, int NTW_, int WV_, int MT_, bool CNF_, int NO_, bool RES_>
+struct Shape {
+  typedef Op_ Op;
+  static constexpr int NTW = NTW_, WV = WV_, MT = MT_, NO = NO_;
+  static constexpr bool CNF = CNF_, RES = RES_;
+  static constexpr int H = NTW * 16 * WV, NKH = H / 32, RT = 16 * MT;
+  static constexpr int OM = CNF ? 1 : MT;  // row tiles that own state
+  static constexpr int PR = CNF ? 8 * MT : RT;  // instances
+  static constexpr int SA = H + 8, PA = RT * SA;
+  // both hidden layers' outputs in LDS while two buffers are small
+  static constexpr bool DB = 2 * Op::kA * PA * 2 <= 56 * 1024;
+  // weight k blocks in flight: about 32 registers of ring, 2 to 4 blocks
+  static constexpr int P = NTW * Op::kW >= 4 ? 2 : 4;
+  // LDS offsets known at compile time: biases, layer buffers
+  static constexpr int oFv = 0, oA = 4 * (3 * H + 256);
+  static constexpr int oT = oA + 2 * Op::kA * PA * (DB ? 2 : 1);
+  static constexpr int oX = oT + 4 * 32;
+};
+
+// The network, from the host.
+struct Net {
+  int B, D, din, H;  // H: the width of act_out rows
+  int nk1, nn3, ks;  // k blocks of layer 1, output tiles, k split
+  size_t off2, off3, plane;
+  const uint16_t* w;
+  const float* fvec;
+  const float* eps;
+};
+
+__host__ __device__ inline int k_split(int nn3, int wv, int nkh) {
+  int k = 1;
+  while (nn3 * 2 * k <= wv && 2 * k <= nkh) k *= 2;
+  return k;
+}
+
+// Byte offsets of a tile's LDS.
+struct Lds {
+  int red, ldot, end;
+  int sx, px;
+};
+
+template <class S>
+__host__ __device__ inline Lds lds_map(int din) {
+  const int nk1 = (din + 31) / 32, nn3 = din / 16;
+  const int ks = k_split(nn3, S::WV, S::NKH);
+  Lds l;
+  l.sx = nk1 * 32 + 8;
+  l.px = S::RT * l.sx;
+  l.red = S::oX + 2 * S::Op::kA * l.px;
+  l.ldot = l.red + (ks - 1) * nn3 * S::MT * 1024;
+  l.end = l.ldot + (S::CNF ? 4 * nn3 * S::PR : 0);
+  l.end = (l.end + 15) / 16 * 16;
+  return l;
+}
+
+typedef mtile::Bf3 PackOp;
+
+// One k block's weight fragments of NT feature tiles.
+template <class S, int NT>
+struct Frag {
+  bf16x8 f[NT][S::Op::kW];
+};
+
+template <class S, int NT>
+__device__ __forceinline__ void load_frag(Frag<S, NT>& d, const uint16_t* W,
+                                          size_t plane, int kb, int nn,
+                                          int nb0, int lane) {
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int p = 0; p < S::Op::kW; ++p)
+      // uniform fragment address, the lane's 16 bytes as a 32-bit offset
+      d.f[t][p] = *reinterpret_cast<const bf16x8*>(
+          reinterpret_cast<const char*>(
+              W + p * plane + ((size_t)(kb * nn + nb0 + t)) * 512) +
+          (unsigned)lane * 16u);
+}
+
+// C^T[MT][NT] += W^T block x A^T block (k block kb of the rows in LDS at A).
+template <class S, int NT>
+__device__ __forceinline__ void products(f32x4 (&acc)[S::MT][NT],
+                                         const Frag<S, NT>& w,
+                                         const uint16_t* A, int plane,
+                                         int stride, int kb, int lane) {
+  typedef typename S::Op Op;
+  bf16x8 b[S::MT][Op::kA];
+#pragma unroll
+  for (int m = 0; m < S::MT; ++m)
+#pragma unroll
+    for (int p = 0; p < Op::kA; ++p)
+      b[m][p] = mtile::lds8(A + p * plane + (m * 16 + (lane & 15)) * stride +
+                            kb * 32 + (lane >> 4) * 8);
+#pragma unroll
+  for (int q = 0; q < Op::kN; ++q)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int m = 0; m < S::MT; ++m)
+        acc[m][t] = mtile::mfma(w.f[t][Op::kTerm[q][0]],
+                                b[m][Op::kTerm[q][1]], acc[m][t]);
+}
+
+// Weight stream of one layer: k blocks k0 .. k0 + nk - 1, P in flight.
+template <class S, int NT>
+struct Stream {
+  Frag<S, NT> r[S::P];
+  __device__ __forceinline__ void start(const uint16_t* W, size_t plane,
+                                        int k0, int nk, int nn, int nb0,
+                                        int lane) {
+#pragma unroll
+    for (int p = 0; p < S::P; ++p)
+      load_frag<S, NT>(r[p], W, plane, k0 + (p < nk ? p : nk - 1), nn, nb0,
+                       lane);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __device__ __forceinline__ void run(f32x4 (&acc)[S::MT][NT],
+                                      const uint16_t* W, size_t plane, int k0,
+                                      int nk, int nn, int nb0,
+                                      const uint16_t* A, int aplane,
+                                      int stride, int lane) {
+    for (int i = 0; i < nk; i += S::P) {
+#pragma unroll
+      for (int p = 0; p < S::P; ++p) {
+        if (i + p >= nk) break;
+        products<S, NT>(acc, r[p], A, aplane, stride, k0 + i + p, lane);
+        const int nx = i + p + S::P;
+        load_frag<S, NT>(r[p], W, plane, k0 + (nx < nk ? nx : nk - 1), nn,
+                         nb0, lane);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+};
+
+// The weights of a launch: resident, or the streams' rings.
+template <class S, bool RES = S::RES>
+struct Weights {
+  Stream<S, S::NTW> s1, s2;
+  Stream<S, 1> s3[S::NO];
+};
+template <class S>
+struct Weights<S, true> {
+  Frag<S, S::NTW> w1[2], w2[S::NKH];
+  Frag<S, 1> w3[S::NKH / 2];
+};
+
+template <class S>
+struct Tile {
+  typedef typename S::Op Op;
+  typedef f32x4 Vec[S::OM][S::NO];  // this lane's elements of a state vector
+  const Net& n;
+  Lds l;
+  unsigned char* sm;
+  int tid, lane, wave, c, q;  // c: column (row of the tile), q: feature group
+  int nb3, kh, k0, nk3;       // output layer: tile, k split, k blocks
+  bool owner;                 // this wavefront owns state elements
+  Weights<S> w;
+
+  __device__ __forceinline__ uint16_t* X() const {
+    return reinterpret_cast<uint16_t*>(sm + S::oX);
+  }
+  __device__ __forceinline__ uint16_t* A(int i) const {
+    return reinterpret_cast<uint16_t*>(sm + S::oA) +
+           (S::DB ? i * Op::kA * S::PA : 0);
+  }
+  __device__ __forceinline__ f32x4* red() const {
+    return reinterpret_cast<f32x4*>(sm + l.red);
+  }
+  __device__ __forceinline__ float* ldot() const {
+    return reinterpret_cast<float*>(sm + l.ldot);
+  }
+  __device__ __forceinline__ float* tcol() const {
+    return reinterpret_cast<float*>(sm + S::oT);
+  }
+  __device__ __forceinline__ float* fv() const {
+    return reinterpret_cast<float*>(sm + S::oFv);
+  }
+  // output tile and its first feature for owned tile o; whether it exists
+  __device__ __forceinline__ int nb_of(int o) const {
+    return S::NO == 1 ? nb3 : wave + o * S::WV;
+  }
+  __device__ __forceinline__ int f0(int o) const {
+    return nb_of(o) * 16 + q * 4;
+  }
+  __device__ __forceinline__ bool has(int o) const {
+    return owner && nb_of(o) < n.nn3;
+  }
+
+  __device__ __forceinline__ Tile(const Net& net, unsigned char* smem)
+      : n(net), l(lds_map<S>(net.din)), sm(smem) {
+    tid = threadIdx.x;
+    lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    c = lane & 15;
+    q = lane >> 4;
+    if (S::NO == 1) {
+      nb3 = wave % n.nn3;
+      kh = wave / n.nn3;
+      owner = kh == 0;
+      nk3 = S::NKH / n.ks;
+      k0 = kh * nk3;
+    } else {
+      nb3 = wave;
+      kh = 0;
+      owner = wave < n.nn3;
+      nk3 = S::NKH;
+      k0 = 0;
+    }
+    for (int i = tid; i < 3 * S::H + n.din; i += 64 * S::WV)
+      fv()[i] = n.fvec[i];
+    if constexpr (S::RES) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+        load_frag<S, S::NTW>(w.w1[kb], n.w, n.plane, kb < n.nk1 ? kb : 0,
+                             S::H / 16, wave * S::NTW, lane);
+#pragma unroll
+      for (int kb = 0; kb < S::NKH; ++kb)
+        load_frag<S, S::NTW>(w.w2[kb], n.w + n.off2, n.plane, kb, S::H / 16,
+                             wave * S::NTW, lane);
+#pragma unroll
+      for (int kb = 0; kb < S::NKH / 2; ++kb)
+        load_frag<S, 1>(w.w3[kb], n.w + n.off3, n.plane,
+                        kh < n.ks && kb < nk3 ? k0 + kb : 0, n.nn3, nb3, lane);
+    } else {
+      start1();
+    }
+  }
+
+  __device__ __forceinline__ void start1() {
+    if constexpr (!S::RES)
+      w.s1.start(n.w, n.plane, 0, n.nk1, S::H / 16, wave * S::NTW, lane);
+  }
+
+  // Constant parts of the layer-1 input: zero columns beyond the state, and
+  // for the CNF the probe on the tangent rows (ep: this lane's elements).
+  __device__ __forceinline__ void begin(const Vec& ep) {
+    const int w1 = n.nk1 * 32 - n.din;
+    for (int i = tid; i < S::RT * w1; i += 64 * S::WV)
+#pragma unroll
+      for (int p = 0; p < Op::kA; ++p)
+        X()[p * l.px + (i / w1) * l.sx + n.din + i % w1] = 0;
+    if (S::CNF) {
+#pragma unroll
+      for (int o = 0; o < S::NO; ++o)
+        if (has(o) && (S::MT == 2 || c < 8))
+          put4<Op::kA, false>(X() + (c + S::PR) * l.sx + f0(o), l.px,
+                              ep[0][o]);
+    }
+  }
+
+  // The stage input into LDS.
+  __device__ __forceinline__ void put_input(const Vec& Y) {
+#pragma unroll
+    for (int o = 0; o < S::NO; ++o)
+#pragma unroll
+      for (int m = 0; m < S::OM; ++m)
+        if (has(o) && (!S::CNF || S::MT == 2 || c < 8))
+          put4<Op::kA, true>(X() + (m * 16 + c) * l.sx + f0(o), l.px,
+                             Y[m][o]);
+  }
+
+  // tanh layer LAYER from buffer `in`; act: the layer values of row r0 + r
+  // are stored there (MfmaArgs::act_out), or null.
+  template <int LAYER>
+  __device__ __forceinline__ void hidden(const uint16_t* in, int plane,
+                                         int stride, float* act, int r0) {
+    f32x4 acc[S::MT][S::NTW];
+#pragma unroll
+    for (int m = 0; m < S::MT; ++m)
+#pragma unroll
+      for (int t = 0; t < S::NTW; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (S::RES) {
+      if constexpr (LAYER == 0) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+          if (kb < n.nk1)
+            products<S, S::NTW>(acc, w.w1[kb], in, plane, stride, kb, lane);
+      } else {
+#pragma unroll
+        for (int kb = 0; kb < S::NKH; ++kb)
+          products<S, S::NTW>(acc, w.w2[kb], in, plane, stride, kb, lane);
+      }
+    } else if constexpr (LAYER == 0) {
+      w.s1.run(acc, n.w, n.plane, 0, n.nk1, S::H / 16, wave * S::NTW, in,
+               plane, stride, lane);
+      w.s2.start(n.w + n.off2, n.plane, 0, S::NKH, S::H / 16, wave * S::NTW,
+                 lane);
+    } else {
+      w.s2.run(acc, n.w + n.off2, n.plane, 0, S::NKH, S::H / 16,
+               wave * S::NTW, in, plane, stride, lane);
+#pragma unroll
+      for (int o = 0; o < S::NO; ++o)
+        if (S::NO == 1 ? kh < n.ks : nb_of(o) < n.nn3)
+          w.s3[o].start(n.w + n.off3, n.plane, k0, nk3, n.nn3, nb_of(o), lane);
+    }
+    // in place: every wave has read its input first
+    if (!S::DB && LAYER == 1) __syncthreads();
+    const float* bias = fv() + (LAYER == 0 ? 0 : 2 * S::H);
+    const float* w1t = fv() + S::H;
+    uint16_t* out = A(LAYER);
+    float tc[S::OM];
+#pragma unroll
+    for (int m = 0; m < S::OM; ++m)
+      tc[m] = LAYER == 0 ? tcol()[S::CNF && S::MT == 1 ? (c & 7) : m * 16 + c]
+                         : 0.f;
+#pragma unroll
+    for (int t = 0; t < S::NTW; ++t) {
+      const int f = (wave * S::NTW + t) * 16 + q * 4;
+      const f32x4 b = *reinterpret_cast<const f32x4*>(bias + f);
+      f32x4 wt{0.f, 0.f, 0.f, 0.f};
+      if (LAYER == 0) wt = *reinterpret_cast<const f32x4*>(w1t + f);
+#pragma unroll
+      for (int m = 0; m < S::OM; ++m) {
+        const bool prim = !S::CNF || S::MT == 2 || c < 8;
+        f32x4 a, keep = acc[m][t], ta{}, tk{};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float v = acc[m][t][i] + b[i];
+          if (LAYER == 0) v += tc[m] * wt[i];
+          a[i] = fast_tanh(v);
+        }
+        if (S::CNF && S::MT == 2) {  // tangents: the other tile, same lane
+          tk = acc[S::MT - 1][t];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            ta[i] = fmaf(-a[i], a[i], 1.f) * tk[i];
+        } else if (S::CNF) {  // tangents: the lanes 8 places away
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float ap = xor8(a[i]);
+            if (!prim) a[i] = fmaf(-ap, ap, 1.f) * keep[i];
+          }
+        }
+        put4<Op::kA, false>(out + (m * 16 + c) * S::SA + f, S::PA, a);
+        if (S::CNF && S::MT == 2)
+          put4<Op::kA, false>(out + (16 + c) * S::SA + f, S::PA, ta);
+        if (act != nullptr) {
+          // activations of primal rows, pre-activation tangents of tangents
+          const int g = r0 + (prim ? m * 16 + c : c - 8);
+          if (g < n.B) {
+            float* p =
+                act + ((size_t)(g + (prim ? 0 : n.B)) * 2 + LAYER) * n.H + f;
+            put_act(p, prim ? a : keep, f);
+            if (S::CNF && S::MT == 2)
+              put_act(p + (size_t)n.B * 2 * n.H, tk, f);
+          }
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void put_act(float* p, f32x4 v, int f) const {
+    if ((n.H & 3) == 0) {
+      if (f < n.H) *reinterpret_cast<f32x4*>(p) = v;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (f + i < n.H) p[i] = v[i];
+    }
+  }
+
+  // k = f(t, Y) for the rows of the tile: Y's elements are in LDS
+  // (put_input), the stage time in tcol; kl: the CNF's log-density
+  // derivative of row c (in every owning lane).  Barriers: one at entry,
+  // one after each layer; the caller may write the next input as soon as
+  // this returns.
+  __device__ __forceinline__ void eval(Vec& k, float& kl, const Vec& ep,
+                                       float* act, int r0) {
+    __syncthreads();
+    hidden<0>(X(), l.px, l.sx, act, r0);
+    __syncthreads();
+    hidden<1>(A(0), S::PA, S::SA, act, r0);
+    __syncthreads();
+    const uint16_t* in = A(1);
+    f32x4 acc[S::NO][S::MT][1];
+#pragma unroll
+    for (int o = 0; o < S::NO; ++o) {
+#pragma unroll
+      for (int m = 0; m < S::MT; ++m)
+        acc[o][m][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const bool on = S::NO == 1 ? kh < n.ks : nb_of(o) < n.nn3;
+      if (on) {
+        if constexpr (S::RES) {
+#pragma unroll
+          for (int kb = 0; kb < S::NKH / 2; ++kb)
+            if (kb < nk3)
+              products<S, 1>(acc[o], w.w3[kb], in, S::PA, S::SA, k0 + kb,
+                             lane);
+        } else {
+          w.s3[o].run(acc[o], n.w + n.off3, n.plane, k0, nk3, n.nn3, nb_of(o),
+                      in, S::PA, S::SA, lane);
+        }
+        if (S::NO == 1 && kh > 0)
+#pragma unroll
+          for (int m = 0; m < S::MT; ++m)
+            red()[(((kh - 1) * n.nn3 + nb3) * S::MT + m) * 64 + lane] =
+                acc[o][m][0];
+      }
+    }
+    start1();
+    if (S::NO == 1 && n.ks > 1) __syncthreads();
+#pragma unroll
+    for (int o = 0; o < S::NO; ++o) {
+      if (!has(o)) continue;
+      if (S::NO == 1)
+        for (int j = 0; j + 1 < n.ks; ++j)
+#pragma unroll
+          for (int m = 0; m < S::MT; ++m)
+            acc[o][m][0] += red()[((j * n.nn3 + nb3) * S::MT + m) * 64 + lane];
+      const f32x4 b = *reinterpret_cast<const f32x4*>(fv() + 3 * S::H + f0(o));
+#pragma unroll
+      for (int m = 0; m < S::OM; ++m) k[m][o] = acc[o][m][0] + b;
+      if (S::CNF) {
+        // eps . (dg/dz eps): over this lane's features, then the four
+        // feature groups; the output tiles meet in LDS
+        const f32x4 v = acc[o][S::MT - 1][0];
+        float d = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d = fmaf(ep[0][o][i], v[i], d);
+        d += __shfl_xor(d, 16, 64);
+        d += __shfl_xor(d, 32, 64);
+        if (q == 0 && (S::MT == 2 || c >= 8))
+          ldot()[nb_of(o) * S::PR + (S::MT == 2 ? c : c - 8)] = d;
+      }
+    }
+    if (S::CNF) {
+      __syncthreads();
+      float s = 0.f;
+      if (owner)
+        for (int nb = 0; nb < n.nn3; ++nb)
+          s += ldot()[nb * S::PR + (S::MT == 2 ? c : (c & 7))];
+      kl = -s;
+    }
+  }
+};
+
+}  // namespace ntile
+}  // namespace bode
