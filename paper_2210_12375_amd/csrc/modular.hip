@@ -34,6 +34,7 @@
 #include "modular.hpp"
 #include "mlp_mfma.hpp"
 #include "mlp_mfma_tile.hpp"
+#include "neural_bwd.hpp"
 #include "neural_fwd.hpp"
 #include "tableau.hpp"
 
@@ -105,7 +106,9 @@ struct Back {
   // vector-Jacobian products run, with its own step view act2, bh2, bt2.
   R* Yst;
   R* Ast;
+  // (seg 0: the store holds one step only, recomputed for each in turn)
   size_t yst_half, ast_half;
+  int seg;
   int32_t* act2;
   R* bh2;
   double* bt2;
@@ -1050,6 +1053,7 @@ size_t lay_mod(const bode_config& c, void* base, Mod<R>* m, MfmaWeights* mw,
     const size_t store = (size_t)k * 7 * (B * D + Bs * 2 * H) * sizeof(R);
     if ((uses_mfma(c, din) || uses_f64(c, din)) &&
         store <= (size_t(2) << 30)) {
+      bk.seg = 1;
       bk.yst_half = (size_t)k * 7 * B * D;
       bk.ast_half = (size_t)k * 7 * Bs * 2 * H;
       bk.Yst = L.take<R>(2 * bk.yst_half);
@@ -1057,6 +1061,9 @@ size_t lay_mod(const bode_config& c, void* base, Mod<R>* m, MfmaWeights* mw,
       bk.act2 = L.take<int32_t>(B);
       bk.bh2 = L.take<R>(B);
       bk.bt2 = L.take<double>(B);
+    } else if (c.precision == BODE_BF16) {
+      bk.Yst = L.take<R>(7 * B * D);
+      bk.Ast = L.take<R>(7 * Bs * 2 * H);
     }
   }
   MfmaWeights w{};
@@ -1875,6 +1882,44 @@ MfmaVjpArgs vjp_args(const ModImpl& im, const Mod<float>& m,
   return a;
 }
 
+// BF16 mode: the adjoint stages of one step (or, mu set, one stage) from
+// the stored stage inputs Yh and layers Ah of its seven stages.
+BwdArgs bwd_args(const Mod<float>& m, const Back<float>& b, const float* Yh,
+                 const float* Ah, long kbase) {
+  BwdArgs a{};
+  a.B = m.B;
+  a.D = m.D;
+  a.eps = m.eps;
+  for (int st = 0; st < 7; ++st) {
+    a.Y[st] = Yh + (size_t)st * m.B * m.D;
+    a.act[st] = Ah + (size_t)st * m.B * (m.cnf ? 2 : 1) * 2 * m.H;
+  }
+  a.T1in = b.T1in;
+  a.T1g = b.T1g;
+  a.T2in = b.T2in;
+  a.T2g = b.T2g;
+  a.T3in = b.T3in;
+  a.T3g = b.T3g;
+  a.kb = kbase;
+  a.Bs = m.cnf ? 2L * m.B : (long)m.B;
+  a.lam = b.lam;
+  return a;
+}
+
+hipError_t launch_bwd(const ModImpl& im, const Mod<float>& m,
+                      const BwdArgs& a, const TableauArgs& tab,
+                      hipStream_t s) {
+  BwdCall c{};
+  c.a = &a;
+  c.tab = &tab;
+  c.din = m.d_in;
+  c.H = m.H;
+  c.cnf = m.cnf;
+  c.waves = get_tune(im.cfg).waves;
+  c.w = im.mw;
+  return bwd_run(c, s);
+}
+
 // The FP64 matrix-core VJP's arguments.
 F64VjpArgs vjp_args64(const Mod<double>& m, const Back<double>& b,
                       const VjpSpec& sp) {
@@ -2635,7 +2680,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
   // VJPs on the matrix cores (FP64: only on stored layers)
   const bool mat = std::is_same<R, float>::value
                        ? im.mw.packedT != nullptr
-                       : m.wpT != nullptr && b.Yst != nullptr;
+                       : m.wpT != nullptr && b.seg;
   if (!mat) {
     // tape inputs of tiles no step writes must be finite (they meet 0); the
     // matrix-core VJP kernels write zeros into those rows themselves
@@ -2705,8 +2750,10 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
     // FP64 always takes the one launch
     typename std::conditional<std::is_same<R, float>::value, MfmaVjpSteps,
                               F64VjpSteps>::type vs{};
+    [[maybe_unused]] const bool bf16 =
+        std::is_same<R, float>::value && mat && !im.mw.f32 && few_tiles(m);
     const bool steps =
-        mat && (!std::is_same<R, float>::value || few_tiles(m));
+        mat && (!std::is_same<R, float>::value || bf16 || few_tiles(m));
     if (steps) {
       {
         VjpDenseT<R>& d = vs.dense;
@@ -2742,7 +2789,18 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
       hipLaunchKernelGGL(fill_r<R>, lin_grid((long)m.d_in * rows), blk, 0, s,
                          b.T3g + kbase * m.d_in, (long)m.d_in * rows, R(0));
     }
-    for (int st = 7; st >= 1; --st) {
+    if constexpr (std::is_same<R, float>::value) {
+      if (bf16) {
+        BwdArgs a = bwd_args(m, b, Yh + (size_t)j * 7 * BD,
+                             Ah + (size_t)j * 7 * m.B * (m.cnf ? 2 : 1) * 2 *
+                                      m.H,
+                             kbase);
+        a.dense = vs.dense;
+        const hipError_t r = launch_bwd(im, m, a, tableau_args<M>(), s);
+        if (r != hipSuccess) return r;
+      }
+    }
+    for (int st = bf16 ? 0 : 7; st >= 1; --st) {
       VjpSpec sp{};
       sp.s = st;
       sp.c = M::C[st - 1];
@@ -2769,7 +2827,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
       const hipError_t r = vjp<R>(im, m, b, sp, s);
       if (r != hipSuccess) return r;
     }
-    if (steps) {
+    if (steps && !bf16) {
       hipError_t r;
       if constexpr (std::is_same<R, float>::value)
         r = launch_vjp_steps_mfma(vs, s);
@@ -2808,7 +2866,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
     }
     return hipSuccess;
   };
-  if (b.Yst != nullptr) {
+  if (b.seg) {
     // Segment store, pipelined over two streams: segment q - 1 is
     // recomputed on the second stream (its stage inputs and layers into
     // store half (q - 1) & 1) while the caller's stream runs segment q's
@@ -2893,11 +2951,13 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
         }
       }
       R* yn = b.yseg + (size_t)(n - base) * BD;
+      R* y1 = b.Yst != nullptr ? b.Yst : b.Ys;
       hipLaunchKernelGGL(adj_setup<R>, rows_g, blk, 0, s, m, b, n,
-                         (const R*)yn, b.Ys);
+                         (const R*)yn, y1);
       v.st.y = yn;
-      e = stages<R, M>(im, v, b, nullptr, true, s);
-      if (e == hipSuccess) e = back_step(n, nullptr, nullptr, 0, 0);
+      e = b.Yst != nullptr ? stages_store<R, M>(im, v, b, 0, s)
+                           : stages<R, M>(im, v, b, nullptr, true, s);
+      if (e == hipSuccess) e = back_step(n, b.Yst, b.Ast, 0, 0);
       if (e != hipSuccess) return e;
     }
   }

@@ -1,4 +1,5 @@
-// Host dispatch of the forward kernels by hidden width.
+// Host dispatch of the neural-field kernels by hidden width.
+#include "neural_bwd.hpp"
 #include "neural_fwd.hpp"
 
 namespace bode {
@@ -64,6 +65,16 @@ hipError_t fwd_stage(const MfmaArgs& a, hipStream_t s) {
   c.waves = a.waves;
   c.w = a.w;
   return by_width(c, s);
+}
+
+hipError_t bwd_run(const BwdCall& c, hipStream_t s) {
+  switch (c.H) {
+    case 512: return bwd_h512(c, s);
+    case 256: return bwd_h256(c, s);
+    case 128: return bwd_h128(c, s);
+    case 64: return bwd_h64(c, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace bode

@@ -310,8 +310,9 @@ struct Tile {
       nk3 = S::NKH;
       k0 = 0;
     }
-    for (int i = tid; i < 3 * S::H + n.din; i += 64 * S::WV)
-      fv()[i] = n.fvec[i];
+    if (n.fvec != nullptr)
+      for (int i = tid; i < 3 * S::H + n.din; i += 64 * S::WV)
+        fv()[i] = n.fvec[i];
     if constexpr (S::RES) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -363,11 +364,11 @@ struct Tile {
                              Y[m][o]);
   }
 
-  // tanh layer LAYER from buffer `in`; act: the layer values of row r0 + r
-  // are stored there (MfmaArgs::act_out), or null.
-  template <int LAYER>
-  __device__ __forceinline__ void hidden(const uint16_t* in, int plane,
-                                         int stride, float* act, int r0) {
+  // The products of hidden layer LAYER (0 or 1) from buffer `in`, then
+  // epi(acc) once the output buffer may be written.
+  template <int LAYER, class Epi>
+  __device__ __forceinline__ void layer(const uint16_t* in, int plane,
+                                        int stride, Epi epi) {
     f32x4 acc[S::MT][S::NTW];
 #pragma unroll
     for (int m = 0; m < S::MT; ++m)
@@ -399,6 +400,21 @@ struct Tile {
     }
     // in place: every wave has read its input first
     if (!S::DB && LAYER == 1) __syncthreads();
+    epi(acc);
+  }
+
+  // tanh layer LAYER from buffer `in`; act: the layer values of row r0 + r
+  // are stored there (MfmaArgs::act_out), or null.
+  template <int LAYER>
+  __device__ __forceinline__ void hidden(const uint16_t* in, int plane,
+                                         int stride, float* act, int r0) {
+    layer<LAYER>(in, plane, stride, [&](f32x4(&acc)[S::MT][S::NTW]) {
+      tanh_out<LAYER>(acc, act, r0);
+    });
+  }
+  template <int LAYER>
+  __device__ __forceinline__ void tanh_out(f32x4 (&acc)[S::MT][S::NTW],
+                                           float* act, int r0) {
     const float* bias = fv() + (LAYER == 0 ? 0 : 2 * S::H);
     const float* w1t = fv() + S::H;
     uint16_t* out = A(LAYER);
@@ -462,20 +478,10 @@ struct Tile {
     }
   }
 
-  // k = f(t, Y) for the rows of the tile: Y's elements are in LDS
-  // (put_input), the stage time in tcol; kl: the CNF's log-density
-  // derivative of row c (in every owning lane).  Barriers: one at entry,
-  // one after each layer; the caller may write the next input as soon as
-  // this returns.
-  __device__ __forceinline__ void eval(Vec& k, float& kl, const Vec& ep,
-                                       float* act, int r0) {
-    __syncthreads();
-    hidden<0>(X(), l.px, l.sx, act, r0);
-    __syncthreads();
-    hidden<1>(A(0), S::PA, S::SA, act, r0);
-    __syncthreads();
+  // The output layer from A(1), whole in the owning lanes (one barrier when
+  // its k blocks are split).
+  __device__ __forceinline__ void output(f32x4 (&acc)[S::NO][S::MT][1]) {
     const uint16_t* in = A(1);
-    f32x4 acc[S::NO][S::MT][1];
 #pragma unroll
     for (int o = 0; o < S::NO; ++o) {
 #pragma unroll
@@ -502,14 +508,30 @@ struct Tile {
     }
     start1();
     if (S::NO == 1 && n.ks > 1) __syncthreads();
+    if (S::NO == 1 && owner)
+      for (int j = 0; j + 1 < n.ks; ++j)
+#pragma unroll
+        for (int m = 0; m < S::MT; ++m)
+          acc[0][m][0] += red()[((j * n.nn3 + nb3) * S::MT + m) * 64 + lane];
+  }
+
+  // k = f(t, Y) for the rows of the tile: Y's elements are in LDS
+  // (put_input), the stage time in tcol; kl: the CNF's log-density
+  // derivative of row c (in every owning lane).  Barriers: one at entry,
+  // one after each layer; the caller may write the next input as soon as
+  // this returns.
+  __device__ __forceinline__ void eval(Vec& k, float& kl, const Vec& ep,
+                                       float* act, int r0) {
+    __syncthreads();
+    hidden<0>(X(), l.px, l.sx, act, r0);
+    __syncthreads();
+    hidden<1>(A(0), S::PA, S::SA, act, r0);
+    __syncthreads();
+    f32x4 acc[S::NO][S::MT][1];
+    output(acc);
 #pragma unroll
     for (int o = 0; o < S::NO; ++o) {
       if (!has(o)) continue;
-      if (S::NO == 1)
-        for (int j = 0; j + 1 < n.ks; ++j)
-#pragma unroll
-          for (int m = 0; m < S::MT; ++m)
-            acc[o][m][0] += red()[((j * n.nn3 + nb3) * S::MT + m) * 64 + lane];
       const f32x4 b = *reinterpret_cast<const f32x4*>(fv() + 3 * S::H + f0(o));
 #pragma unroll
       for (int m = 0; m < S::OM; ++m) k[m][o] = acc[o][m][0] + b;
@@ -536,6 +558,47 @@ struct Tile {
     }
   }
 };
+
+// Elements f .. f + 3 of a row of `lim` (zero beyond).
+__device__ __forceinline__ f32x4 row4(const float* p, int f, int lim,
+                                      bool vec) {
+  if (vec && f + 3 < lim) return *reinterpret_cast<const f32x4*>(p + f);
+  f32x4 v{};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = f + i < lim ? p[f + i] : 0.f;
+  return v;
+}
+__device__ __forceinline__ void put_row4(float* p, int f, int lim, bool vec,
+                                         f32x4 v) {
+  if (vec && f + 3 < lim) {
+    *reinterpret_cast<f32x4*>(p + f) = v;
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (f + i < lim) p[f + i] = v[i];
+}
+
+// acc += a * v, skipped for a zero coefficient (uniform).
+__device__ __forceinline__ void axpy(f32x4& acc, float a, f32x4 v) {
+  if (a != 0.f) acc += a * v;
+}
+
+constexpr size_t kLdsMax = 160 * 1024;
+
+template <class K, class A>
+hipError_t launch(K kernel, int grid, int block, size_t sm, const A& args,
+                  hipStream_t s) {
+  if (sm > kLdsMax) return hipErrorInvalidValue;
+  if (sm > 65536) {
+    const hipError_t e = hipFuncSetAttribute(
+        reinterpret_cast<const void*>(kernel),
+        hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), sm, s, args);
+  return hipGetLastError();
+}
 
 }  // namespace ntile
 }  // namespace bode
