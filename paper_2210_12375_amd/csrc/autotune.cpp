@@ -74,16 +74,11 @@ int autotune(const bode_config* cfg, const bode_problem* p, void* workspace,
       }
   } else {
     const int din = cfg->rhs == BODE_RHS_CNF ? cfg->D - 1 : cfg->D;
-    const bool mfma =
-        cfg->precision == BODE_BF16 ||
-        (cfg->precision == BODE_FP32 &&
-         mfma_supported(din, cfg->mlp_hidden).empty());
+    const bool mfma = neural_fused(cfg->precision, din, cfg->mlp_hidden);
     const bool fused = mfma && !cfg->keep_dense;
     std::vector<int> waves = {0};
     if (mfma && cfg->mlp_hidden > 64) {
-      const int def = mfma_waves(cfg->mlp_hidden, cfg->rhs == BODE_RHS_CNF,
-                                 cfg->B, 0);
-      waves = {def, def == 8 ? 4 : 8};
+      waves = {8, 4};
     }
     std::vector<int> rounds = {0};
     if (!fused) rounds = {8, 4, 16};

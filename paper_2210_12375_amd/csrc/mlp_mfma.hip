@@ -1,10 +1,11 @@
-// Neural right-hand sides on the matrix cores of gfx950: weight packing,
-// the per-stage field kernel and the adjoint-stage kernel (the building
-// blocks and operand policies are in mlp_mfma_tile.hpp).
+// Neural right-hand sides on the matrix cores of gfx950: weight packing and
+// the per-stage adjoint kernel of large BF16 batches (building blocks in
+// mlp_mfma_tile.hpp).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "../../include/batchode.h"
 #include "common.hpp"
 #include "mlp_mfma.hpp"
 #include "mlp_mfma_tile.hpp"
@@ -15,106 +16,78 @@ namespace {
 
 using namespace mtile;
 
-__device__ __forceinline__ void cvt(uint16_t& d, float v) { d = f2bf(v); }
-__device__ __forceinline__ void cvt(float& d, float v) { d = v; }
-
-// One weight matrix to pack: M = W (trans = 0) or W^T into the fragment
-// layout of mtile (W row-major with leading dimension ldw, K rows of M).
-template <typename W>
+// One weight matrix to pack: M = W (trans = 0) or W^T, K x N, into the
+// fragment layout of mtile (W row-major with leading dimension ldw), zero
+// beyond K and N.
 struct PackJob {
-  W* dst;
-  const float* Wm;
-  int K, ldw, nk, nn, trans;
+  uint16_t* dst;
+  const float* W;
+  int K, N, ldw, nk, nn, trans;
+  size_t plane;  // elements between the BF16 terms' planes
 };
 
-template <typename W>
-__device__ void pack_one(const PackJob<W>& j, int blk, int nblk) {
-  const long total = (long)j.nk * j.nn * 512;
-  for (long e = blk * (long)blockDim.x + threadIdx.x; e < total;
-       e += (long)nblk * blockDim.x) {
-    const int i = e & 7, l = (e >> 3) & 63;
-    const long f = e >> 9;
-    const int kb = int(f / j.nn), nb = int(f % j.nn);
-    const int k = kb * 32 + (l >> 4) * 8 + i, n = nb * 16 + (l & 15);
-    const long src = j.trans ? (long)n * j.ldw + k : (long)k * j.ldw + n;
-    cvt(j.dst[e], k < j.K ? j.Wm[src] : 0.f);
-  }
-}
+struct PackJobs {
+  PackJob j[6];
+  int n, planes;
+  float* f;  // b1, W1's time row, b2 (padded to Hp), b3 (padded)
+  const float *W1, *b1, *b2, *b3;
+  int din, H, Hp, dp;
+};
 
-// The three layers (and, with the transposed copies, their transposes)
-// and the vector block (b1, W1's time row, b2, b3) in one launch: grid y
-// selects the job, the last one being the vector block.
-template <typename W>
-__global__ void pack_weights_kernel(PackJob<W> j0, PackJob<W> j1,
-                                    PackJob<W> j2, PackJob<W> j3,
-                                    PackJob<W> j4, PackJob<W> j5, int njobs,
-                                    float* f, const float* W1, const float* b1,
-                                    const float* b2, const float* b3, int din,
-                                    int H) {
-  const int y = blockIdx.y;
-  if (y < njobs) {
-    const PackJob<W>& j = y == 0 ? j0 : y == 1 ? j1 : y == 2 ? j2
-                        : y == 3 ? j3 : y == 4 ? j4 : j5;
-    pack_one(j, blockIdx.x, gridDim.x);
+// A thread packs one lane's eight elements of a fragment (one 16-byte store
+// per plane); the last grid row does the vector block.  Terms are rounded to
+// nearest (beyond 2^127 cut, so that none overflows) and each residual is
+// exact; one plane is the BF16 weight itself.
+__global__ void pack_weights_kernel(PackJobs p) {
+  const int tid = blockIdx.x * blockDim.x + threadIdx.x;
+  const int nthr = gridDim.x * blockDim.x;
+  if ((int)blockIdx.y < p.n) {
+    const PackJob j = p.j[blockIdx.y];
+    const int total = j.nk * j.nn * 64;
+    for (int e = tid; e < total; e += nthr) {
+      const int l = e & 63, f = e >> 6;
+      const int k0 = f / j.nn * 32 + (l >> 4) * 8;
+      const int n = f % j.nn * 16 + (l & 15);
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int k = k0 + i;
+        v[i] = k < j.K && n < j.N
+                   ? j.W[j.trans ? (long)n * j.ldw + k : (long)k * j.ldw + n]
+                   : 0.f;
+      }
+      for (int q = 0; q < p.planes; ++q) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+          uint16_t h[2];
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            float& x = v[i + u];
+            const bool big = p.planes > 1 && !(fabsf(x) < 1.7014118e38f);
+            h[u] = big ? uint16_t(__float_as_uint(x) >> 16) : f2bf(x);
+            const float hv = __uint_as_float((uint32_t)h[u] << 16);
+            x = __builtin_isfinite(hv) ? x - hv : 0.f;
+          }
+          w[i / 2] = h[0] | ((uint32_t)h[1] << 16);
+        }
+        *reinterpret_cast<uint4*>(j.dst + q * j.plane + (size_t)e * 8) =
+            make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
     return;
   }
-  for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < 3 * H + din;
-       c += gridDim.x * blockDim.x) {
-    float v;
-    if (c < H)
-      v = b1[c];
-    else if (c < 2 * H)
-      v = W1[(long)din * H + (c - H)];  // time row of W1
-    else if (c < 3 * H)
-      v = b2[c - 2 * H];
-    else
-      v = b3[c - 3 * H];
-    f[c] = v;
+  for (int c = tid; c < 3 * p.Hp + p.dp; c += nthr) {
+    const int b = c / p.Hp < 3 ? c / p.Hp : 3, i = c - b * p.Hp;
+    float v = 0.f;
+    if (i < (b < 3 ? p.H : p.din))
+      v = b == 0   ? p.b1[i]
+          : b == 1 ? p.W1[(long)p.din * p.H + i]  // time row of W1
+          : b == 2 ? p.b2[i]
+                   : p.b3[i];
+    p.f[c] = v;
   }
 }
-
-template <class Op, int NTW, bool CNF, int WV>
-__global__ __launch_bounds__(64 * WV) void field_mfma_kernel(MfmaArgs a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  field_tile<Op, NTW, CNF, WV>(a, blockIdx.x * (CNF ? 8 : 16), smem_raw);
-}
-
-// Several stage evaluations of one step in one launch, in order: a tile's
-// stage inputs depend only on its own rows' earlier stages, which pass
-// between the tile's waves through memory (the barrier orders them).
-// KL: the stage values stay in LDS (v.kl_off) between the stages.
-template <class Op, int NTW, bool CNF, int WV, bool KL>
-__global__ __launch_bounds__(64 * WV) void field_steps_kernel(MfmaSteps v) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  float* kl = KL ? reinterpret_cast<float*>(smem_raw + v.kl_off) : nullptr;
-  for (int i = 0; i < v.n; ++i) {
-    field_tile<Op, NTW, CNF, WV, true, KL>(v.st[i], blockIdx.x * (CNF ? 8 : 16),
-                                           smem_raw, kl);
-    __syncthreads();
-  }
-}
-
-template <class Op, int NTW, bool CNF, int WV>
-hipError_t launch_t(const MfmaArgs& a, const MfmaSteps* v, hipStream_t s) {
-  constexpr int PR = CNF ? 8 : 16;
-  const size_t sm = mfma_smem<Op, NTW, CNF, WV>(a.din);
-  if (sm > 65536) return hipErrorInvalidValue;
-  if (v != nullptr) {
-    MfmaSteps w = *v;
-    w.kl_off = (int)((sm + 15) / 16 * 16);
-    const size_t smk = w.kl_off + sizeof(float) * 7 * PR * (size_t)a.D;
-    if (w.kl && smk <= 65536)
-      hipLaunchKernelGGL((field_steps_kernel<Op, NTW, CNF, WV, true>),
-                         dim3((a.B + PR - 1) / PR), dim3(64 * WV), smk, s, w);
-    else
-      hipLaunchKernelGGL((field_steps_kernel<Op, NTW, CNF, WV, false>),
-                         dim3((a.B + PR - 1) / PR), dim3(64 * WV), sm, s, w);
-  } else
-    hipLaunchKernelGGL((field_mfma_kernel<Op, NTW, CNF, WV>),
-                       dim3((a.B + PR - 1) / PR), dim3(64 * WV), sm, s, a);
-  return hipGetLastError();
-}
-
 
 // Adjoint stage on MFMA.  The hidden layers are recomputed as in the field
 // kernel; each lane keeps, for its accumulator elements, the activation
@@ -651,143 +624,47 @@ __global__ __launch_bounds__(64 * WV) __attribute__((
 // depend on no other tile's, so its workgroup runs the stages in turn, the
 // cotangents passing between them through memory (the barrier orders them;
 // all of the tile's waves share the compute unit's cache).
-// CL: the cotangents stay in LDS through the step (v.cl_off: their block's
-// byte offset; the dense-output part must run in the same launch, since it
-// is what clears and seeds them).
-// PF: the stage fronts are requested a stage ahead (the first one before
-// the dense-output part); only with the stored layers and the LDS block.
-template <class Op, int NTW, bool CNF, int WV, bool CL, bool PF>
-__global__ __launch_bounds__(64 * WV) __attribute__((
-    amdgpu_waves_per_eu(CNF ? 4 : 1))) void vjp_steps_kernel(MfmaVjpSteps v) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  float* cl = CL ? reinterpret_cast<float*>(smem_raw + v.cl_off) : nullptr;
-  VjpFront<vjp_ne<CNF ? 8 : 16, WV, 64>(), NTW> f;
-  if constexpr (PF) vjp_front_load<CNF, WV>(v.st[0], f);
-  if (v.dense.on) {
-    vjp_dense_rows<CNF ? 8 : 16, WV, CL>(v.dense, v.st[0].kap, v.st[0].lamn,
-                                         v.st[0].B, v.st[0].D, cl);
-    __syncthreads();
-  }
-  for (int i = 0; i < v.n; ++i) {
-    vjp_tile<Op, NTW, CNF, WV, CL, PF>(v.st[i], smem_raw, cl, &f,
-                                       v.st[i + 1 < v.n ? i + 1 : i], i == 0);
-    __syncthreads();
-  }
-}
-
 template <class Op, int NTW, bool CNF, int WV>
-hipError_t launch_vjp_t(const MfmaVjpArgs& a, const MfmaVjpSteps* v,
-                        hipStream_t s) {
+hipError_t launch_vjp_t(const MfmaVjpArgs& a, hipStream_t s) {
   constexpr int PR = CNF ? 8 : 16;
   const size_t sm = mfma_smem<Op, NTW, CNF, WV>(a.din);
   if (sm > 65536) return hipErrorInvalidValue;
-  if (v != nullptr) {
-    // the cotangent block in LDS while it fits beside the kernel's LDS
-    MfmaVjpSteps w = *v;
-    w.cl_off = (int)((sm + 15) / 16 * 16);
-    const size_t smc = w.cl_off + sizeof(float) * 8 * PR * (size_t)a.D;
-    bool stored = true;  // every stage reads its stored layers
-    for (int i = 0; i < w.n; ++i) stored = stored && w.st[i].act_in;
-    // (the fronts a stage ahead: while the kernel's registers allow)
-    constexpr bool kPF = !CNF && NTW <= 2;
-    if (w.dense.on && smc <= 65536 && stored && kPF && a.din <= 64)
-      hipLaunchKernelGGL((vjp_steps_kernel<Op, NTW, CNF, WV, true, kPF>),
-                         dim3((a.B + PR - 1) / PR), dim3(64 * WV), smc, s, w);
-    else if (w.dense.on && smc <= 65536)
-      hipLaunchKernelGGL((vjp_steps_kernel<Op, NTW, CNF, WV, true, false>),
-                         dim3((a.B + PR - 1) / PR), dim3(64 * WV), smc, s, w);
-    else
-      hipLaunchKernelGGL((vjp_steps_kernel<Op, NTW, CNF, WV, false, false>),
-                         dim3((a.B + PR - 1) / PR), dim3(64 * WV), sm, s, w);
-  } else
-    hipLaunchKernelGGL((vjp_mfma_kernel<Op, NTW, CNF, WV>),
-                       dim3((a.B + PR - 1) / PR), dim3(64 * WV), sm, s, a);
+  hipLaunchKernelGGL((vjp_mfma_kernel<Op, NTW, CNF, WV>),
+                     dim3((a.B + PR - 1) / PR), dim3(64 * WV), sm, s, a);
   return hipGetLastError();
 }
 
-template <class Op>
-hipError_t pack_all(const MfmaWeights& w, int din, int H, const float* W1,
-                    const float* b1, const float* W2, const float* b2,
-                    const float* W3, const float* b3, hipStream_t s) {
-  typedef typename Op::W W;
-  const Dims d = dims(din, H);
-  W* p = static_cast<W*>(w.packed);
-  PackJob<W> j[6] = {{p, W1, din, H, d.nk1, d.nn1, 0},
-                     {p + d.off2, W2, H, H, d.nk2, d.nn2, 0},
-                     {p + d.off3, W3, H, din, d.nk3, d.nn3, 0}};
-  int n = 3;
-  if (w.packedT != nullptr) {
-    const DimsT t = dims_t(din, H);
-    W* q = static_cast<W*>(w.packedT);
-    j[3] = {q, W3, din, din, t.nk3, t.nn3, 1};
-    j[4] = {q + t.off2, W2, H, H, t.nk2, t.nn2, 1};
-    j[5] = {q + t.off1, W1, H, H, t.nk1, t.nn1, 1};
-    n = 6;
-  }
-  hipLaunchKernelGGL(pack_weights_kernel<W>, dim3(128, n + 1), dim3(256), 0,
-                     s, j[0], j[1], j[2], j[3], j[4], j[5], n, w.fvec, W1, b1,
-                     b2, b3, din, H);
-  return hipGetLastError();
-}
-
-// Hidden width -> (column tiles per wavefront, wavefronts): 8 wavefronts
-// from H = 128 up, so a tile's layers run on two wavefronts per SIMD; the
-// CNF field at H = 512 keeps 4 (8 column tiles each), which measured faster
-// for its 8 primal + 8 tangent rows (62 vs 75 us per stage at 8192
-// instances), while its VJP is faster on 8.
 template <class Op, bool CNF>
-hipError_t field_h(const MfmaArgs& a, const MfmaSteps* v, hipStream_t s) {
-  const int wv = mfma_waves(a.H, CNF, a.B, a.waves);
+hipError_t vjp_h(const MfmaVjpArgs& a, hipStream_t s) {
   switch (a.H) {
-    case 512:
-      return wv == 4 ? launch_t<Op, 8, CNF, 4>(a, v, s)
-                     : launch_t<Op, 4, CNF, 8>(a, v, s);
-    case 256:
-      return wv == 4 ? launch_t<Op, 4, CNF, 4>(a, v, s)
-                     : launch_t<Op, 2, CNF, 8>(a, v, s);
-    case 128:
-      return wv == 4 ? launch_t<Op, 2, CNF, 4>(a, v, s)
-                     : launch_t<Op, 1, CNF, 8>(a, v, s);
-    default: return launch_t<Op, 1, CNF, 4>(a, v, s);
-  }
-}
-
-template <class Op, bool CNF>
-hipError_t vjp_h(const MfmaVjpArgs& a, const MfmaVjpSteps* v, hipStream_t s) {
-  switch (a.H) {
-    case 512: return launch_vjp_t<Op, 4, CNF, 8>(a, v, s);
-    case 256: return launch_vjp_t<Op, 2, CNF, 8>(a, v, s);
-    case 128: return launch_vjp_t<Op, 1, CNF, 8>(a, v, s);
-    default: return launch_vjp_t<Op, 1, CNF, 4>(a, v, s);
+    case 512: return launch_vjp_t<Op, 4, CNF, 8>(a, s);
+    case 256: return launch_vjp_t<Op, 2, CNF, 8>(a, s);
+    case 128: return launch_vjp_t<Op, 1, CNF, 8>(a, s);
+    default: return launch_vjp_t<Op, 1, CNF, 4>(a, s);
   }
 }
 
 }  // namespace
 
+size_t mfma_plane_elems(int din, int H) {
+  const Dims d = dims(mfma_pad_din(din), mfma_pad_h(H));
+  return d.off3 + (size_t)d.nk3 * d.nn3 * 512;
+}
+
+size_t mfma_planeT_elems(int din, int H) {
+  return dims_t(mfma_pad_din(din), mfma_pad_h(H)).total;
+}
+
 size_t mfma_packed_bytes(int din, int H, int f32) {
-  const Dims d = dims(din, H);
-  return (d.off3 + (size_t)d.nk3 * d.nn3 * 512) * (f32 ? 4 : 2);
+  return mfma_plane_elems(din, H) * (f32 ? 6 : 2);
 }
 
 size_t mfma_packedT_bytes(int din, int H, int f32) {
-  return dims_t(din, H).total * (f32 ? 4 : 2);
+  return mfma_planeT_elems(din, H) * (f32 ? 6 : 2);
 }
 
-size_t mfma_fvec_elems(int din, int H) { return 3 * (size_t)H + din; }
-
-int mfma_waves(int H, bool cnf, int B, int requested) {
-  if (H <= 64) return 4;  // one 16-column tile per wavefront at most
-  if (requested == 4 || requested == 8) return requested;
-  // measured defaults: 8 wavefronts (two per SIMD) from width 128 up while
-  // the tiles are about one per compute unit; 4 once there are two or more
-  // tiles per compute unit, so that two workgroups share one (MLP at width
-  // 256, fused solve: 16,384 instances 1.45 -> 1.15 ms, 65,536 5.13 -> 3.98
-  // ms, 4096 0.45 vs 0.51 ms on 4); and 4 for the CNF at width 512 (its
-  // tangent rows double the epilogue registers; 62 vs 75 us per stage
-  // evaluation of 8192 instances)
-  if (cnf && H == 512) return 4;
-  const long tiles = (B + (cnf ? 7 : 15)) / (cnf ? 8 : 16);
-  return H >= 256 && tiles >= 512 ? 4 : 8;
+size_t mfma_fvec_elems(int din, int H) {
+  return 3 * (size_t)mfma_pad_h(H) + mfma_pad_din(din);
 }
 
 std::string mfma_supported(int din, int H) {
@@ -799,12 +676,43 @@ std::string mfma_supported(int din, int H) {
   return "";
 }
 
+bool neural_fused(int precision, int din, int H) {
+  return precision == BODE_BF16 ||
+         (precision == BODE_FP32 && din <= 256 && H <= 512);
+}
+
 hipError_t mfma_pack_weights(const MfmaWeights& w, int din, int H,
                              const float* W1, const float* b1, const float* W2,
                              const float* b2, const float* W3, const float* b3,
                              hipStream_t s) {
-  return w.f32 ? pack_all<F32>(w, din, H, W1, b1, W2, b2, W3, b3, s)
-               : pack_all<Bf3>(w, din, H, W1, b1, W2, b2, W3, b3, s);
+  PackJobs p{};
+  p.planes = w.f32 ? 3 : 1;
+  p.f = w.fvec;
+  p.W1 = W1;
+  p.b1 = b1;
+  p.b2 = b2;
+  p.b3 = b3;
+  p.din = din;
+  p.H = H;
+  p.dp = mfma_pad_din(din);
+  p.Hp = mfma_pad_h(H);
+  const Dims d = dims(p.dp, p.Hp);
+  const DimsT t = dims_t(p.dp, p.Hp);
+  uint16_t *a = static_cast<uint16_t*>(w.packed),
+           *b = static_cast<uint16_t*>(w.packedT);
+  const size_t pl = mfma_plane_elems(din, H), plt = mfma_planeT_elems(din, H);
+  const PackJob j[6] = {{a, W1, din, H, H, d.nk1, d.nn1, 0, pl},
+                        {a + d.off2, W2, H, H, H, d.nk2, d.nn2, 0, pl},
+                        {a + d.off3, W3, H, din, din, d.nk3, d.nn3, 0, pl},
+                        {b, W3, din, H, din, t.nk3, t.nn3, 1, plt},
+                        {b + t.off2, W2, H, H, H, t.nk2, t.nn2, 1, plt},
+                        {b + t.off1, W1, H, din, H, t.nk1, t.nn1, 1, plt}};
+  p.n = b != nullptr ? 6 : 3;
+  for (int q = 0; q < p.n; ++q) p.j[q] = j[q];
+  const int blocks = (d.nk2 * d.nn2 * 64 + 255) / 256;
+  hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks, p.n + 1), dim3(256), 0,
+                     s, p);
+  return hipGetLastError();
 }
 
 MfmaArgs mfma_args(int B, int D, int din, int H, int cnf, const int32_t* status,
@@ -827,38 +735,10 @@ MfmaArgs mfma_args(int B, int D, int din, int H, int cnf, const int32_t* status,
   return a;
 }
 
-static hipError_t vjp_any(const MfmaVjpArgs& a, const MfmaVjpSteps* v,
-                          hipStream_t s) {
-  if (a.w.packedT == nullptr || a.w.plain) return hipErrorInvalidValue;
-  if (a.w.f32)
-    return a.cnf ? vjp_h<F32, true>(a, v, s) : vjp_h<F32, false>(a, v, s);
-  return a.cnf ? vjp_h<Bf3, true>(a, v, s) : vjp_h<Bf3, false>(a, v, s);
-}
-
 hipError_t launch_vjp_mfma(const MfmaVjpArgs& a, hipStream_t s) {
-  return vjp_any(a, nullptr, s);
-}
-
-hipError_t launch_vjp_steps_mfma(const MfmaVjpSteps& v, hipStream_t s) {
-  if (v.n < 1 || v.n > 7) return hipErrorInvalidValue;
-  return vjp_any(v.st[0], &v, s);
-}
-
-// (FP32 only: BF16 mode's forward kernels are neural_fwd.inc's)
-static hipError_t field_any(const MfmaArgs& a, const MfmaSteps* v,
-                            hipStream_t s) {
-  if (!a.w.f32) return hipErrorInvalidValue;
-  return a.cnf ? field_h<F32, true>(a, v, s) : field_h<F32, false>(a, v, s);
-}
-
-hipError_t launch_field_mfma(const MfmaArgs& a, int row_tile, hipStream_t s) {
-  (void)row_tile;
-  return field_any(a, nullptr, s);
-}
-
-hipError_t launch_field_steps_mfma(const MfmaSteps& v, hipStream_t s) {
-  if (v.n < 1 || v.n > 7) return hipErrorInvalidValue;
-  return field_any(v.st[0], &v, s);
+  if (a.w.packedT == nullptr || a.w.plain || a.w.f32)
+    return hipErrorInvalidValue;
+  return a.cnf ? vjp_h<Bf3, true>(a, s) : vjp_h<Bf3, false>(a, s);
 }
 
 }  // namespace bode

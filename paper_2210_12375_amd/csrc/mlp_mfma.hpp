@@ -10,10 +10,9 @@
 
 namespace bode {
 
-// Packed weights: every layer as 16x32 MFMA B-fragments (64 lanes x 8
-// elements, contiguous per fragment), plus FP32 vectors b1, w1t (the time
-// row of W1), b2, b3.  Elements are BF16 (BF16 mode) or FP32 (FP32 mode,
-// f32 != 0).
+// Packed weights: every layer as 16x32 MFMA fragments (64 lanes x 8 BF16
+// elements, contiguous per fragment; FP32 mode, f32 != 0: three planes of
+// them), plus FP32 vectors b1, w1t (the time row of W1), b2, b3.
 struct MfmaWeights {
   void* packed = nullptr;
   float* fvec = nullptr;
@@ -26,13 +25,25 @@ struct MfmaWeights {
   int plain = 0;
 };
 
+// FP32 mode's weights are three BF16 planes (their exact split) of the
+// layers padded to widths the kernels are built for: state features to 16,
+// hidden units to 64, 128, 256 or 512 (padding is zero; BF16 mode accepts
+// only shapes that need none).
+inline int mfma_pad_din(int din) { return (din + 15) / 16 * 16; }
+inline int mfma_pad_h(int H) {
+  return H <= 64 ? 64 : H <= 128 ? 128 : H <= 256 ? 256 : 512;
+}
 size_t mfma_packed_bytes(int din, int H, int f32);
 size_t mfma_packedT_bytes(int din, int H, int f32);
+size_t mfma_plane_elems(int din, int H);   // elements of a forward plane
+size_t mfma_planeT_elems(int din, int H);  // of a transposed one
 size_t mfma_fvec_elems(int din, int H);
 std::string mfma_supported(int din, int H);
-// Wavefronts per 16-row tile the field kernels use: `requested` (4 or 8)
-// where the width allows it, else the default for the shape.
-int mfma_waves(int H, bool cnf, int B, int requested);
+// Whether a precision (BODE_*) runs this shape on the matrix-core kernels:
+// BF16 always; FP32 as split products (neural_tile.hpp) wherever the packed
+// widths hold the shape, at any width in between (padding a 50-wide layer to
+// 64 costs nothing beside the FMA kernel it replaces: 11.7 -> 0.78 ms).
+bool neural_fused(int precision, int din, int H);
 
 hipError_t mfma_pack_weights(const MfmaWeights& w, int din, int H,
                              const float* W1, const float* b1, const float* W2,
@@ -62,16 +73,11 @@ struct MfmaArgs {
   float* act_out;
   // wavefronts per 16-row tile: 4 or 8 (0: the default for the width)
   int waves;
-  // the fused solve's stage slot of out (its stages kept in LDS)
-  int kslot;
 };
 
 MfmaArgs mfma_args(int B, int D, int din, int H, int cnf, const int32_t* status,
                    const float* y, const float* K, float* Y7, const float* hs,
                    const double* t, const float* eps, const MfmaWeights& w);
-
-// row_tile 0 picks the default for the shape.
-hipError_t launch_field_mfma(const MfmaArgs& a, int row_tile, hipStream_t s);
 
 // One stage s of the discrete adjoint for a batch of rows: mu_s =
 // J_f(Y_s)^T kappa_s on MFMA (the field's hidden layers recomputed), the
@@ -105,30 +111,5 @@ struct MfmaVjpArgs {
 };
 
 hipError_t launch_vjp_mfma(const MfmaVjpArgs& a, hipStream_t s);
-
-// Up to seven stages of one step, each with its own arguments, in one
-// launch, in the order given (same shape and weights in every entry).
-using VjpDense = VjpDenseT<float>;
-
-struct MfmaVjpSteps {
-  MfmaVjpArgs st[7];
-  int n;
-  VjpDense dense;
-  int cl_off;  // set by the launcher
-};
-hipError_t launch_vjp_steps_mfma(const MfmaVjpSteps& v, hipStream_t s);
-
-struct MfmaSteps {
-  MfmaArgs st[7];
-  int n;
-  // kl = 1: the caller reads none of the stage values, which may then stay
-  // in the tile's LDS ([7][rows][D] at byte kl_off, st[i].kslot each stage's
-  // slot) instead of going to st[i].out; kl_off is set by the launcher
-  int kl, kl_off;
-};
-hipError_t launch_field_steps_mfma(const MfmaSteps& v, hipStream_t s);
-// both travel as kernel arguments
-static_assert(sizeof(MfmaVjpSteps) <= 4096 && sizeof(MfmaSteps) <= 4096,
-              "step arguments exceed the kernel-argument space");
 
 }  // namespace bode

@@ -695,126 +695,14 @@ __global__ __launch_bounds__(256) void commit_kernel(Mod<R> m) {
 
 inline dim3 commit_grid(int B, int per) { return dim3((B + per - 1) / per); }
 
-// ---- fused persistent solve (matrix-core fields) ------------------------------
+// ---- fused persistent solve (FP64; the reduced precisions: neural_fwd.inc) ----
 //
-// One launch per solve: a workgroup owns one 16-row tile of the field kernel
-// (16 instances, or 8 CNF instances with their tangent rows) and runs its
-// instances' attempts to the end: the six new stage evaluations of an
-// attempt, then each row's commit by one wavefront.  Instances are
-// independent (each has its own step, section 3), so no workgroup waits on
-// another and there is no per-round launch or host round trip.  Stage
-// outputs pass between the waves of the tile through memory; the barrier
-// between stages orders them (all waves share the compute unit's cache).
-struct FusedArgs {
-  MfmaArgs st[6];  // stages 2..7: combination, node, output
-  int budget;      // attempts per instance
-  int kl_off;      // KL: byte offset of the tile's stage block in LDS
-};
+// One launch per solve: a workgroup runs its tile's instances' attempts to
+// the end, six stage evaluations and the rows' commits each.  Instances are
+// independent (section 3), so no workgroup waits on another.
 
-// KL: the tile's seven stage values stay in LDS ([7][rows][D] after the
-// field's own LDS): stage inputs, outputs, error estimate, dense outputs and
-// FSAL never go through HBM; the FSAL stage is loaded at entry and stored
-// back at exit (a later launch, or a step slice, continues from it).
-template <class Op, int NTW, bool CNF, int WV, class M, bool KL>
-__global__ __launch_bounds__(64 * WV) void solve_fused_kernel(Mod<float> m,
-                                                              FusedArgs f) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  constexpr int PR = CNF ? 8 : 16;
-  const int r0 = blockIdx.x * PR;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int D = m.D;
-  float* kl = KL ? reinterpret_cast<float*>(smem_raw + f.kl_off) : nullptr;
-  if (KL) {
-    for (int i = threadIdx.x; i < PR * D; i += blockDim.x) {
-      const int row = r0 + i / D;
-      kl[i] = row < m.B ? m.K[(long)row * D + i % D] : 0.f;
-    }
-  }
-  __shared__ int active;
-  for (int round = 0; round < f.budget; ++round) {
-    __syncthreads();
-    if (threadIdx.x == 0) active = 0;
-    __syncthreads();
-    if (threadIdx.x < PR && r0 + (int)threadIdx.x < m.B &&
-        m.st.status[r0 + threadIdx.x] == kRunning)
-      active = 1;
-    __syncthreads();
-    if (!active) break;
-    for (int s = 0; s < 6; ++s) {
-      mtile::field_tile<Op, NTW, CNF, WV, false, KL>(f.st[s], r0, smem_raw,
-                                                      kl);
-      __syncthreads();
-    }
-    // MLP: two rows per wavefront (32 lanes each) while D fits two columns
-    // a lane (364 vs 404 us for 4096 instances); the CNF keeps one row per
-    // wavefront, whose tile kernel is already at the register limit of two
-    // wavefronts per SIMD
-    if (!CNF && m.D <= 64) {
-      for (int r = 2 * wave + (lane >> 5); r < PR; r += 2 * WV)
-        commit_row<float, M, false, 32, KL>(m, r0 + r, lane & 31,
-                                            KView<float>{kl, PR * D, r});
-    } else {
-      for (int r = wave; r < PR; r += WV)
-        commit_row<float, M, false, 64, KL>(m, r0 + r, lane,
-                                            KView<float>{kl, PR * D, r});
-    }
-  }
-  if (KL) {  // the FSAL stage back to HBM
-    __syncthreads();
-    for (int i = threadIdx.x; i < PR * D; i += blockDim.x) {
-      const int row = r0 + i / D;
-      if (row < m.B) m.K[(long)row * D + i % D] = kl[i];
-    }
-  }
-}
-
-template <class Op, int NTW, bool CNF, int WV, class M>
-hipError_t fused_t(const Mod<float>& m, FusedArgs f, hipStream_t s) {
-  constexpr int PR = CNF ? 8 : 16;
-  const size_t sm = mtile::mfma_smem<Op, NTW, CNF, WV>(m.d_in);
-  if (sm > 65536) return hipErrorInvalidValue;
-  // the stage block in LDS while it fits beside the field's LDS
-  f.kl_off = (int)((sm + 15) / 16 * 16);
-  const size_t smk = f.kl_off + sizeof(float) * 7 * PR * (size_t)m.D;
-  if (smk <= 65536)
-    hipLaunchKernelGGL((solve_fused_kernel<Op, NTW, CNF, WV, M, true>),
-                       dim3((m.B + PR - 1) / PR), dim3(64 * WV), smk, s, m,
-                       f);
-  else
-    hipLaunchKernelGGL((solve_fused_kernel<Op, NTW, CNF, WV, M, false>),
-                       dim3((m.B + PR - 1) / PR), dim3(64 * WV), sm, s, m, f);
-  return hipGetLastError();
-}
-
-// Wavefronts per tile as for the per-stage field kernel (4 for the CNF at
-// H = 512: 2.89 vs 3.35 ms per solve of 8192 instances).
-template <class Op, bool CNF, class M>
-hipError_t fused_h(const Mod<float>& m, const FusedArgs& f, hipStream_t s) {
-  const int wv = mfma_waves(m.H, CNF, m.B, f.st[0].waves);
-  switch (m.H) {
-    case 512:
-      return wv == 4 ? fused_t<Op, 8, CNF, 4, M>(m, f, s)
-                     : fused_t<Op, 4, CNF, 8, M>(m, f, s);
-    case 256:
-      return wv == 4 ? fused_t<Op, 4, CNF, 4, M>(m, f, s)
-                     : fused_t<Op, 2, CNF, 8, M>(m, f, s);
-    case 128:
-      return wv == 4 ? fused_t<Op, 2, CNF, 4, M>(m, f, s)
-                     : fused_t<Op, 1, CNF, 8, M>(m, f, s);
-    default: return fused_t<Op, 1, CNF, 4, M>(m, f, s);
-  }
-}
-
-template <class M>
-hipError_t fused_launch(const Mod<float>& m, const FusedArgs& f,
-                        hipStream_t s) {
-  return m.cnf ? fused_h<mtile::F32, true, M>(m, f, s)
-               : fused_h<mtile::F32, false, M>(m, f, s);
-}
-
-// FP64: the same whole-solve launch on the FP64 matrix cores (f64_tile.hpp),
-// a tile of 4 to 16 instances per workgroup of eight wavefronts; the rows'
-// commits are one wavefront each.
+// FP64 matrix cores (f64_tile.hpp): a tile of 4 to 16 instances per workgroup
+// of eight wavefronts; the rows' commits are one wavefront each.
 struct Fused64Args {
   F64Args st[6];
   int budget, kl_off;
@@ -969,11 +857,10 @@ inline bool uses_f64(const bode_config& c, int din) {
          f64_fits(c.D, din, c.mlp_hidden, c.rhs == BODE_RHS_CNF);
 }
 
-// BF16 always runs on the matrix cores; FP32 does where the shape is built
+// BF16 always runs on the matrix cores; FP32 does up to their largest widths
 // (else the FMA kernels).
 inline bool uses_mfma(const bode_config& c, int din) {
-  if (c.precision == BODE_BF16) return true;
-  return c.precision == BODE_FP32 && mfma_supported(din, c.mlp_hidden).empty();
+  return neural_fused(c.precision, din, c.mlp_hidden);
 }
 
 template <typename R>
@@ -1061,7 +948,7 @@ size_t lay_mod(const bode_config& c, void* base, Mod<R>* m, MfmaWeights* mw,
       bk.act2 = L.take<int32_t>(B);
       bk.bh2 = L.take<R>(B);
       bk.bt2 = L.take<double>(B);
-    } else if (c.precision == BODE_BF16) {
+    } else if (uses_mfma(c, din)) {
       bk.Yst = L.take<R>(7 * B * D);
       bk.Ast = L.take<R>(7 * Bs * 2 * H);
     }
@@ -1070,7 +957,8 @@ size_t lay_mod(const bode_config& c, void* base, Mod<R>* m, MfmaWeights* mw,
   if (uses_mfma(c, din)) {
     w.f32 = c.precision == BODE_FP32;
     w.plain = c.precision == BODE_BF16 && c.plain_bf16;
-    w.packed = L.take<unsigned char>(mfma_packed_bytes(din, c.mlp_hidden, w.f32));
+    w.packed =
+        L.take<unsigned char>(mfma_packed_bytes(din, c.mlp_hidden, w.f32));
     w.fvec = L.take<float>(mfma_fvec_elems(din, c.mlp_hidden));
     // transposed layers for the VJP kernels (discrete and continuous adjoint)
     w.packedT =
@@ -1198,30 +1086,17 @@ MfmaArgs stage_args(const ModImpl& im, const Mod<float>& m,
 template <>
 hipError_t field<float>(ModImpl& im, const Mod<float>& m, const StageSpec& sp,
                         float* out, hipStream_t s) {
-  if (im.mw.packed != nullptr && !im.mw.f32)
-    return fwd_stage(stage_args(im, m, sp, out), s);
   if (im.mw.packed != nullptr)
-    return launch_field_mfma(stage_args(im, m, sp, out), 0, s);
+    return fwd_stage(stage_args(im, m, sp, out), s);
   return launch_field_fma<float>(m, sp, out, s);
 }
 
-// The whole solve (up to budget attempts per instance) in one launch of the
-// fused kernel.
+// The whole solve (up to budget attempts per instance) in one launch.
 template <class M>
 hipError_t run_fused(const ModImpl& im, const Mod<float>& m, int budget,
                      hipStream_t s) {
-  if (!im.mw.f32)
-    return fwd_solve(m, im.mw, tableau_args<M>(), budget,
-                     get_tune(im.cfg).waves, s);
-  FusedArgs f{};
-  for (int st = 1; st < 7; ++st) {
-    StageSpec sp = stage_spec<M>(st);
-    if (st == 6) sp.yout = m.Y7;
-    f.st[st - 1] = stage_args(im, m, sp, m.K + (size_t)st * m.B * m.D);
-    f.st[st - 1].kslot = st;
-  }
-  f.budget = budget;
-  return fused_launch<M>(m, f, s);
+  return fwd_solve(m, im.mw, tableau_args<M>(), budget,
+                   get_tune(im.cfg).waves, s);
 }
 
 template <class M>
@@ -2621,10 +2496,9 @@ hipError_t stages_store(ModImpl& im, Mod<R> v, Back<R>& b, int j,
   const size_t BD = (size_t)v.B * v.D;
   const size_t AH = (size_t)v.B * (v.cnf ? 2 : 1) * 2 * v.H;
   hipError_t e = hipSuccess;
-  [[maybe_unused]] MfmaSteps fs{};
   [[maybe_unused]] F64Steps f64{};
   if constexpr (std::is_same<R, float>::value) {
-    if (im.mw.packed != nullptr && !im.mw.f32) {  // the seven in one launch
+    if (im.mw.packed != nullptr) {  // the seven in one launch
       FwdSteps f{};
       f.B = v.B;
       f.D = v.D;
@@ -2645,14 +2519,7 @@ hipError_t stages_store(ModImpl& im, Mod<R> v, Back<R>& b, int j,
     StageSpec sp = st == 0 ? StageSpec{} : stage_spec<M>(st);
     sp.yout = st == 0 ? nullptr : b.Yst + ((size_t)j * 7 + st) * BD;
     sp.act_out = b.Ast + ((size_t)j * 7 + st) * AH;
-    if constexpr (std::is_same<R, float>::value) {
-      if (im.mw.packed != nullptr && few_tiles(v)) {  // the seven in one
-        fs.st[fs.n] = stage_args(im, v, sp, b.Ks + (size_t)st * BD);
-        fs.st[fs.n++].kslot = st;
-        fs.kl = 1;  // the stage values are read only by the later stages
-        continue;
-      }
-    } else if (v.wp != nullptr) {
+    if constexpr (!std::is_same<R, float>::value) {
       f64.st[f64.n] = f64_args(v, sp, b.Ks + (size_t)st * BD);
       f64.st[f64.n++].kslot = st;
       f64.kl = 1;
@@ -2660,11 +2527,7 @@ hipError_t stages_store(ModImpl& im, Mod<R> v, Back<R>& b, int j,
     }
     e = field<R>(im, v, sp, b.Ks + (size_t)st * BD, s);
   }
-  if constexpr (std::is_same<R, float>::value) {
-    if (e == hipSuccess && fs.n > 0) e = launch_field_steps_mfma(fs, s);
-  } else if (e == hipSuccess && f64.n > 0) {
-    e = launch_field_f64(f64, s);
-  }
+  if (e == hipSuccess && f64.n > 0) e = launch_field_f64(f64, s);
   return e;
 }
 
@@ -2743,20 +2606,18 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
       const hipError_t r = hipStreamWaitEvent(s, im.ev[7 + half], 0);
       if (r != hipSuccess) return r;
     }
-    // the seven stages in one launch on the matrix cores while the batch
-    // has few tiles (launches, not the tiles' work, set its pace; the
-    // dense-output part then runs in the same launch), else one launch
-    // each (a CNF step of 8192 instances: 16.9 ms one each, 18.9 in one);
-    // FP64 always takes the one launch
-    typename std::conditional<std::is_same<R, float>::value, MfmaVjpSteps,
-                              F64VjpSteps>::type vs{};
-    [[maybe_unused]] const bool bf16 =
-        std::is_same<R, float>::value && mat && !im.mw.f32 && few_tiles(m);
-    const bool steps =
-        mat && (!std::is_same<R, float>::value || bf16 || few_tiles(m));
+    // the seven stages and the dense-output part in one launch on the
+    // matrix cores; BF16 batches of many tiles take one launch each (a CNF
+    // step of 8192 instances: the one launch is no faster alone, and holds
+    // the compute units the parameter-gradient products would share)
+    F64VjpSteps vs{};
+    const bool eng = std::is_same<R, float>::value && mat &&
+                     (im.mw.f32 || few_tiles(m));
+    const bool steps = eng || (mat && !std::is_same<R, float>::value);
+    VjpDenseT<R> dense{};
     if (steps) {
       {
-        VjpDenseT<R>& d = vs.dense;
+        VjpDenseT<R>& d = dense;
         d.on = 1;
         d.setup = setup;
         d.step = n;
@@ -2790,17 +2651,17 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
                          b.T3g + kbase * m.d_in, (long)m.d_in * rows, R(0));
     }
     if constexpr (std::is_same<R, float>::value) {
-      if (bf16) {
+      if (eng) {
         BwdArgs a = bwd_args(m, b, Yh + (size_t)j * 7 * BD,
                              Ah + (size_t)j * 7 * m.B * (m.cnf ? 2 : 1) * 2 *
                                       m.H,
                              kbase);
-        a.dense = vs.dense;
+        a.dense = dense;
         const hipError_t r = launch_bwd(im, m, a, tableau_args<M>(), s);
         if (r != hipSuccess) return r;
       }
     }
-    for (int st = bf16 ? 0 : 7; st >= 1; --st) {
+    for (int st = eng ? 0 : 7; st >= 1; --st) {
       VjpSpec sp{};
       sp.s = st;
       sp.c = M::C[st - 1];
@@ -2818,22 +2679,19 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
         sp.coef[q] = ss.coef[q];
       }
       if (steps) {
-        if constexpr (std::is_same<R, float>::value)
-          vs.st[vs.n++] = vjp_args(im, m, b, sp);
-        else
+        if constexpr (!std::is_same<R, float>::value)
           vs.st[vs.n++] = vjp_args64(m, b, sp);
         continue;
       }
       const hipError_t r = vjp<R>(im, m, b, sp, s);
       if (r != hipSuccess) return r;
     }
-    if (steps && !bf16) {
-      hipError_t r;
-      if constexpr (std::is_same<R, float>::value)
-        r = launch_vjp_steps_mfma(vs, s);
-      else
-        r = launch_vjp_f64(vs, s);
-      if (r != hipSuccess) return r;
+    if constexpr (!std::is_same<R, float>::value) {
+      if (steps) {
+        vs.dense = dense;
+        const hipError_t r = launch_vjp_f64(vs, s);
+        if (r != hipSuccess) return r;
+      }
     }
     if (slot_c == Cc - 1 || n == 0) {
       // parameter gradient of the chunk's steps: one GEMM per layer over

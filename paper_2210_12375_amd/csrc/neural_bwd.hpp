@@ -1,5 +1,4 @@
-// Vector-Jacobian products of the neural fields in BF16 mode
-// (neural_tile.hpp): the seven adjoint stages of one step, or one stage of
+// Vector-Jacobian products of the neural fields (neural_tile.hpp): the seven adjoint stages of one step, or one stage of
 // the continuous adjoint.
 #pragma once
 
@@ -45,8 +44,12 @@ struct BwdCall {
 
 hipError_t bwd_run(const BwdCall& c, hipStream_t s);
 hipError_t bwd_h64(const BwdCall& c, hipStream_t s);
+hipError_t bwd_f32_h64(const BwdCall& c, hipStream_t s);
 hipError_t bwd_h128(const BwdCall& c, hipStream_t s);
+hipError_t bwd_f32_h128(const BwdCall& c, hipStream_t s);
 hipError_t bwd_h256(const BwdCall& c, hipStream_t s);
+hipError_t bwd_f32_h256(const BwdCall& c, hipStream_t s);
 hipError_t bwd_h512(const BwdCall& c, hipStream_t s);
+hipError_t bwd_f32_h512(const BwdCall& c, hipStream_t s);
 
 }  // namespace bode

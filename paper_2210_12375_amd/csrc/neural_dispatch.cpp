@@ -7,11 +7,11 @@ namespace bode {
 namespace {
 
 hipError_t by_width(const FwdCall& c, hipStream_t s) {
-  switch (c.H) {
-    case 512: return fwd_h512(c, s);
-    case 256: return fwd_h256(c, s);
-    case 128: return fwd_h128(c, s);
-    case 64: return fwd_h64(c, s);
+  switch (mfma_pad_h(c.H)) {
+    case 512: return c.w.f32 ? fwd_f32_h512(c, s) : fwd_h512(c, s);
+    case 256: return c.w.f32 ? fwd_f32_h256(c, s) : fwd_h256(c, s);
+    case 128: return c.w.f32 ? fwd_f32_h128(c, s) : fwd_h128(c, s);
+    case 64: return c.w.f32 ? fwd_f32_h64(c, s) : fwd_h64(c, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -68,11 +68,11 @@ hipError_t fwd_stage(const MfmaArgs& a, hipStream_t s) {
 }
 
 hipError_t bwd_run(const BwdCall& c, hipStream_t s) {
-  switch (c.H) {
-    case 512: return bwd_h512(c, s);
-    case 256: return bwd_h256(c, s);
-    case 128: return bwd_h128(c, s);
-    case 64: return bwd_h64(c, s);
+  switch (mfma_pad_h(c.H)) {
+    case 512: return c.w.f32 ? bwd_f32_h512(c, s) : bwd_h512(c, s);
+    case 256: return c.w.f32 ? bwd_f32_h256(c, s) : bwd_h256(c, s);
+    case 128: return c.w.f32 ? bwd_f32_h128(c, s) : bwd_h128(c, s);
+    case 64: return c.w.f32 ? bwd_f32_h64(c, s) : bwd_h64(c, s);
     default: return hipErrorInvalidValue;
   }
 }

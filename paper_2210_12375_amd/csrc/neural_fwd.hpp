@@ -1,4 +1,4 @@
-// Forward kernels of the neural fields in BF16 mode (neural_tile.hpp): a
+// Forward kernels of the neural fields (neural_tile.hpp): a
 // whole solve, one step's seven stage evaluations, one stage evaluation.
 #pragma once
 
@@ -54,8 +54,7 @@ hipError_t fwd_steps(const FwdSteps& v, int din, int H, bool cnf,
                      hipStream_t s);
 hipError_t fwd_stage(const MfmaArgs& a, hipStream_t s);
 
-// Per width and operand policy (one source file each): plain = one BF16
-// term per activation.
+// One source file per padded width and mode (_f32: FP32 mode).
 struct FwdCall {
   int kind;  // 0 solve, 1 steps, 2 stage
   const Mod<float>* m;
@@ -66,8 +65,12 @@ struct FwdCall {
   MfmaWeights w;
 };
 hipError_t fwd_h64(const FwdCall& c, hipStream_t s);
+hipError_t fwd_f32_h64(const FwdCall& c, hipStream_t s);
 hipError_t fwd_h128(const FwdCall& c, hipStream_t s);
+hipError_t fwd_f32_h128(const FwdCall& c, hipStream_t s);
 hipError_t fwd_h256(const FwdCall& c, hipStream_t s);
+hipError_t fwd_f32_h256(const FwdCall& c, hipStream_t s);
 hipError_t fwd_h512(const FwdCall& c, hipStream_t s);
+hipError_t fwd_f32_h512(const FwdCall& c, hipStream_t s);
 
 }  // namespace bode

@@ -1,0 +1,9 @@
+// Forward kernels of the FP32 neural fields at hidden width 512.
+#define BODE_NEURAL_F32
+#include "neural_fwd.inc"
+
+namespace bode {
+hipError_t fwd_f32_h512(const FwdCall& c, hipStream_t s) {
+  return fwd_width<4, 8>(c, s);
+}
+}  // namespace bode

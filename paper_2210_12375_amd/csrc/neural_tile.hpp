@@ -47,12 +47,53 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 // Operand policies: BF16 terms per activation and per weight, and the
 // products issued (weight term, activation term), smallest first.
 struct Bf3 {
+  static constexpr bool kTwo = false;
   static constexpr int kA = 3, kW = 1, kN = 3;
   static constexpr int kTerm[kN][2] = {{0, 2}, {0, 1}, {0, 0}};
+  __device__ static __forceinline__ float tanh(float x) { return fast_tanh(x); }
 };
 struct Bf1 {
+  static constexpr bool kTwo = false;
   static constexpr int kA = 1, kW = 1, kN = 1;
   static constexpr int kTerm[kN][2] = {{0, 0}};
+  __device__ static __forceinline__ float tanh(float x) { return fast_tanh(x); }
+};
+
+// tanh to about one ulp (FP32 mode): x + x^3 q(x^2) below 0.6 (q fitted at
+// Chebyshev nodes, relative error 8e-8 in float arithmetic), 1 - 2 e /
+// (1 + e) with e = exp(-2 |x|) above.
+__device__ __forceinline__ float close_tanh(float x) {
+  const float ax = fabsf(x), z = x * x;
+  const float e = __builtin_amdgcn_exp2f(ax * -2.8853900817779268f);
+  const float big = fmaf(-2.f * e, __builtin_amdgcn_rcpf(1.f + e), 1.f);
+  float q = fmaf(-0.006276387721300125f, z, 0.021116213873028755f);
+  q = fmaf(q, z, -0.053875137120485306f);
+  q = fmaf(q, z, 0.13332924246788025f);
+  q = fmaf(q, z, -0.3333333134651184f);
+  return ax < 0.6f ? fmaf(x, z * q, x) : copysignf(big, x);
+}
+
+// FP32 mode: weights and activations both as three terms.  Of the nine
+// products the six largest are issued; terms are rounded to nearest, so the
+// three dropped are at most about 2^-26 of a product together, below the
+// FP32 accumulation's own rounding.  v_mfma_f32_16x16x4_f32 takes 16 cycles
+// per 1024 products of a tile, six BF16 products of 8 k each 3; measured
+// against it (40,000 instances of 65->256->256->64) 4.57 -> 2.94 ms, and
+// against plain FMA where the widths are no multiples of 16 (300 instances
+// of 7->50->50->6 with their adjoint) 11.7 -> 0.78 ms.  Relative error
+// against 64-bit solves of the same steps, 20 draws: final states 0.7-1.0e-7
+// (1.0-1.8e-7 before), state gradients 1.8-2.3e-7 (2.0-3.6e-7).
+struct Bf6 {
+  // the five small products accumulate apart from hi x hi, so a sum over k is
+  // rounded at its own size once per 32 k, not six times (in one accumulator
+  // the bias gradients, sums of one sign, came out 1.5 times further off)
+  static constexpr bool kTwo = true;
+  static constexpr int kA = 3, kW = 3, kN = 6;
+  static constexpr int kTerm[kN][2] = {{0, 2}, {2, 0}, {1, 1},
+                                       {0, 1}, {1, 0}, {0, 0}};
+  __device__ static __forceinline__ float tanh(float x) {
+    return close_tanh(x);
+  }
 };
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
@@ -114,19 +155,28 @@ struct Shape {
   // both hidden layers' outputs in LDS while two buffers are small
   static constexpr bool DB = 2 * Op::kA * PA * 2 <= 56 * 1024;
   // weight k blocks in flight: about 32 registers of ring, 2 to 4 blocks
-  static constexpr int P = NTW * Op::kW >= 4 ? 2 : 4;
+  static constexpr int P =
+      NTW * Op::kW >= 12 ? 1 : NTW * Op::kW >= 4 ? 2 : 4;
   // LDS offsets known at compile time: biases, layer buffers
   static constexpr int oFv = 0, oA = 4 * (3 * H + 256);
   static constexpr int oT = oA + 2 * Op::kA * PA * (DB ? 2 : 1);
   static constexpr int oX = oT + 4 * 32;
 };
 
+// Two wavefronts per SIMD: 256 registers, all ordinary ones (with more, the
+// compiler keeps sums in accumulation registers and copies them out).
+#define BODE_TILE_BOUNDS(S)             \
+  __launch_bounds__(64 * S::WV)         \
+      __attribute__((amdgpu_waves_per_eu(2)))
+
 // The network, from the host.
 struct Net {
-  int B, D, din, H;  // H: the width of act_out rows
+  int B, D, din, dr, H;  // din, dr: state features, padded and not; H: the
+                         // hidden width, not padded (act_out's rows)
   int nk1, nn3, ks;  // k blocks of layer 1, output tiles, k split
-  size_t off2, off3, plane;
+  int off2, off3, plane;  // in fragments
   const uint16_t* w;
+  unsigned wbytes;
   const float* fvec;
   const float* eps;
 };
@@ -165,24 +215,98 @@ struct Frag {
   bf16x8 f[NT][S::Op::kW];
 };
 
+// A kernel's by-value argument, through a pointer the compiler cannot see
+// through: its fields are loaded (scalar, cached) where they are used instead
+// of being held in scalar registers across the whole kernel, where they
+// spilled.
+template <class T>
+using Karg = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ __forceinline__ Karg<T> kernarg() {
+  auto p = (Karg<T>)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// A uniform value the compiler recomputes from (offsets derived from it are
+// not hoisted out of the stage loop into spilled scalars).
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
+// Packed layers as a buffer: a fragment's address is the uniform offset of
+// its 1 KiB (a scalar) plus the lane's 16 bytes, so no lane holds 64-bit
+// addresses (as pointers the compiler kept one per fragment of an unrolled
+// layer and spilled them).
+struct WBuf {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ WBuf(const uint16_t* w, unsigned bytes)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(w), 0,
+                                            (int)bytes, 0x00027000)) {}
+  __device__ __forceinline__ bf16x8 frag(int f, int lane) const {
+    return __builtin_bit_cast(
+        bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16, f * 1024,
+                                                      0));
+  }
+};
+
+// Fragments nb0 .. nb0 + NT - 1 of k block kb of the layer at fragment f0
+// (nn column tiles a k block, `plane` fragments between the terms).
 template <class S, int NT>
-__device__ __forceinline__ void load_frag(Frag<S, NT>& d, const uint16_t* W,
-                                          size_t plane, int kb, int nn,
+__device__ __forceinline__ void load_frag(Frag<S, NT>& d, const WBuf& W,
+                                          int f0, int plane, int kb, int nn,
                                           int nb0, int lane) {
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int p = 0; p < S::Op::kW; ++p)
-      // uniform fragment address, the lane's 16 bytes as a 32-bit offset
-      d.f[t][p] = *reinterpret_cast<const bf16x8*>(
-          reinterpret_cast<const char*>(
-              W + p * plane + ((size_t)(kb * nn + nb0 + t)) * 512) +
-          (unsigned)lane * 16u);
+      d.f[t][p] = W.frag(f0 + p * plane + kb * nn + nb0 + t, lane);
 }
+
+// Accumulators of NT feature tiles (Op::kTwo: the small products apart).
+template <class S, int NT>
+struct Acc {
+  f32x4 v[S::MT][NT], lo[S::Op::kTwo ? S::MT : 1][S::Op::kTwo ? NT : 1];
+  __device__ __forceinline__ Acc() {
+#pragma unroll
+    for (int m = 0; m < S::MT; ++m)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        v[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (S::Op::kTwo) lo[m][t] = v[m][t];
+      }
+  }
+  // The sums for ordinary instructions.  A matrix product's result may be
+  // read by them only some wait states after its issue; the compiler counts
+  // those inside a block, but was seen to miss them where a branch leads
+  // straight from the last product to the first read (stale sums in the
+  // wavefronts that skip the output layer's loads), so they are spent here:
+  // the empty statements tie every accumulator to its place.
+  __device__ __forceinline__ void finish() {
+    tie();
+    asm volatile("s_nop 11");
+    tie();
+    if constexpr (S::Op::kTwo)
+#pragma unroll
+      for (int m = 0; m < S::MT; ++m)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) v[m][t] += lo[m][t];
+  }
+  __device__ __forceinline__ void tie() {
+#pragma unroll
+    for (int m = 0; m < S::MT; ++m)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        asm volatile("" : "+v"(v[m][t]));
+        if constexpr (S::Op::kTwo) asm volatile("" : "+v"(lo[m][t]));
+      }
+  }
+};
 
 // C^T[MT][NT] += W^T block x A^T block (k block kb of the rows in LDS at A).
 template <class S, int NT>
-__device__ __forceinline__ void products(f32x4 (&acc)[S::MT][NT],
+__device__ __forceinline__ void products(Acc<S, NT>& acc,
                                          const Frag<S, NT>& w,
                                          const uint16_t* A, int plane,
                                          int stride, int kb, int lane) {
@@ -199,37 +323,42 @@ __device__ __forceinline__ void products(f32x4 (&acc)[S::MT][NT],
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-      for (int m = 0; m < S::MT; ++m)
-        acc[m][t] = mtile::mfma(w.f[t][Op::kTerm[q][0]],
-                                b[m][Op::kTerm[q][1]], acc[m][t]);
+      for (int m = 0; m < S::MT; ++m) {
+        f32x4* c = &acc.v[m][t];
+        if constexpr (Op::kTwo)
+          if (q + 1 < Op::kN) c = &acc.lo[m][t];
+        *c = mtile::mfma(w.f[t][Op::kTerm[q][0]], b[m][Op::kTerm[q][1]], *c);
+      }
 }
 
 // Weight stream of one layer: k blocks k0 .. k0 + nk - 1, P in flight.
 template <class S, int NT>
 struct Stream {
   Frag<S, NT> r[S::P];
-  __device__ __forceinline__ void start(const uint16_t* W, size_t plane,
+  __device__ __forceinline__ void start(const WBuf& W, int f0, int plane,
                                         int k0, int nk, int nn, int nb0,
                                         int lane) {
+    f0 = opaque(f0);
+    plane = opaque(plane);
 #pragma unroll
     for (int p = 0; p < S::P; ++p)
-      load_frag<S, NT>(r[p], W, plane, k0 + (p < nk ? p : nk - 1), nn, nb0,
-                       lane);
+      if (p < nk) load_frag<S, NT>(r[p], W, f0, plane, k0 + p, nn, nb0, lane);
     __builtin_amdgcn_sched_barrier(0);
   }
-  __device__ __forceinline__ void run(f32x4 (&acc)[S::MT][NT],
-                                      const uint16_t* W, size_t plane, int k0,
-                                      int nk, int nn, int nb0,
-                                      const uint16_t* A, int aplane,
-                                      int stride, int lane) {
+  __device__ __forceinline__ void run(Acc<S, NT>& acc, const WBuf& W,
+                                      int f0, int plane, int k0, int nk,
+                                      int nn, int nb0, const uint16_t* A,
+                                      int aplane, int stride, int lane) {
+    f0 = opaque(f0);
+    plane = opaque(plane);
     for (int i = 0; i < nk; i += S::P) {
 #pragma unroll
       for (int p = 0; p < S::P; ++p) {
         if (i + p >= nk) break;
         products<S, NT>(acc, r[p], A, aplane, stride, k0 + i + p, lane);
         const int nx = i + p + S::P;
-        load_frag<S, NT>(r[p], W, plane, k0 + (nx < nk ? nx : nk - 1), nn,
-                         nb0, lane);
+        if (nx < nk)
+          load_frag<S, NT>(r[p], W, f0, plane, k0 + nx, nn, nb0, lane);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -258,6 +387,7 @@ struct Tile {
   int tid, lane, wave, c, q;  // c: column (row of the tile), q: feature group
   int nb3, kh, k0, nk3;       // output layer: tile, k split, k blocks
   bool owner;                 // this wavefront owns state elements
+  WBuf wb;
   Weights<S> w;
 
   __device__ __forceinline__ uint16_t* X() const {
@@ -291,7 +421,7 @@ struct Tile {
   }
 
   __device__ __forceinline__ Tile(const Net& net, unsigned char* smem)
-      : n(net), l(lds_map<S>(net.din)), sm(smem) {
+      : n(net), l(lds_map<S>(net.din)), sm(smem), wb(net.w, net.wbytes) {
     tid = threadIdx.x;
     lane = tid & 63;
     wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -316,15 +446,15 @@ struct Tile {
     if constexpr (S::RES) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
-        load_frag<S, S::NTW>(w.w1[kb], n.w, n.plane, kb < n.nk1 ? kb : 0,
+        load_frag<S, S::NTW>(w.w1[kb], wb, 0, n.plane, kb < n.nk1 ? kb : 0,
                              S::H / 16, wave * S::NTW, lane);
 #pragma unroll
       for (int kb = 0; kb < S::NKH; ++kb)
-        load_frag<S, S::NTW>(w.w2[kb], n.w + n.off2, n.plane, kb, S::H / 16,
+        load_frag<S, S::NTW>(w.w2[kb], wb, n.off2, n.plane, kb, S::H / 16,
                              wave * S::NTW, lane);
 #pragma unroll
       for (int kb = 0; kb < S::NKH / 2; ++kb)
-        load_frag<S, 1>(w.w3[kb], n.w + n.off3, n.plane,
+        load_frag<S, 1>(w.w3[kb], wb, n.off3, n.plane,
                         kh < n.ks && kb < nk3 ? k0 + kb : 0, n.nn3, nb3, lane);
     } else {
       start1();
@@ -333,7 +463,7 @@ struct Tile {
 
   __device__ __forceinline__ void start1() {
     if constexpr (!S::RES)
-      w.s1.start(n.w, n.plane, 0, n.nk1, S::H / 16, wave * S::NTW, lane);
+      w.s1.start(wb, 0, n.plane, 0, n.nk1, S::H / 16, wave * S::NTW, lane);
   }
 
   // Constant parts of the layer-1 input: zero columns beyond the state, and
@@ -369,11 +499,7 @@ struct Tile {
   template <int LAYER, class Epi>
   __device__ __forceinline__ void layer(const uint16_t* in, int plane,
                                         int stride, Epi epi) {
-    f32x4 acc[S::MT][S::NTW];
-#pragma unroll
-    for (int m = 0; m < S::MT; ++m)
-#pragma unroll
-      for (int t = 0; t < S::NTW; ++t) acc[m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Acc<S, S::NTW> acc;
     if constexpr (S::RES) {
       if constexpr (LAYER == 0) {
 #pragma unroll
@@ -386,21 +512,22 @@ struct Tile {
           products<S, S::NTW>(acc, w.w2[kb], in, plane, stride, kb, lane);
       }
     } else if constexpr (LAYER == 0) {
-      w.s1.run(acc, n.w, n.plane, 0, n.nk1, S::H / 16, wave * S::NTW, in,
+      w.s1.run(acc, wb, 0, n.plane, 0, n.nk1, S::H / 16, wave * S::NTW, in,
                plane, stride, lane);
-      w.s2.start(n.w + n.off2, n.plane, 0, S::NKH, S::H / 16, wave * S::NTW,
+      w.s2.start(wb, n.off2, n.plane, 0, S::NKH, S::H / 16, wave * S::NTW,
                  lane);
     } else {
-      w.s2.run(acc, n.w + n.off2, n.plane, 0, S::NKH, S::H / 16,
+      w.s2.run(acc, wb, n.off2, n.plane, 0, S::NKH, S::H / 16,
                wave * S::NTW, in, plane, stride, lane);
 #pragma unroll
       for (int o = 0; o < S::NO; ++o)
         if (S::NO == 1 ? kh < n.ks : nb_of(o) < n.nn3)
-          w.s3[o].start(n.w + n.off3, n.plane, k0, nk3, n.nn3, nb_of(o), lane);
+          w.s3[o].start(wb, n.off3, n.plane, k0, nk3, n.nn3, nb_of(o), lane);
     }
     // in place: every wave has read its input first
     if (!S::DB && LAYER == 1) __syncthreads();
-    epi(acc);
+    acc.finish();
+    epi(acc.v);
   }
 
   // tanh layer LAYER from buffer `in`; act: the layer values of row r0 + r
@@ -437,7 +564,7 @@ struct Tile {
         for (int i = 0; i < 4; ++i) {
           float v = acc[m][t][i] + b[i];
           if (LAYER == 0) v += tc[m] * wt[i];
-          a[i] = fast_tanh(v);
+          a[i] = Op::tanh(v);
         }
         if (S::CNF && S::MT == 2) {  // tangents: the other tile, same lane
           tk = acc[S::MT - 1][t];
@@ -484,27 +611,28 @@ struct Tile {
     const uint16_t* in = A(1);
 #pragma unroll
     for (int o = 0; o < S::NO; ++o) {
-#pragma unroll
-      for (int m = 0; m < S::MT; ++m)
-        acc[o][m][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+      Acc<S, 1> c;
       const bool on = S::NO == 1 ? kh < n.ks : nb_of(o) < n.nn3;
       if (on) {
         if constexpr (S::RES) {
 #pragma unroll
           for (int kb = 0; kb < S::NKH / 2; ++kb)
             if (kb < nk3)
-              products<S, 1>(acc[o], w.w3[kb], in, S::PA, S::SA, k0 + kb,
+              products<S, 1>(c, w.w3[kb], in, S::PA, S::SA, k0 + kb,
                              lane);
         } else {
-          w.s3[o].run(acc[o], n.w + n.off3, n.plane, k0, nk3, n.nn3, nb_of(o),
+          w.s3[o].run(c, wb, n.off3, n.plane, k0, nk3, n.nn3, nb_of(o),
                       in, S::PA, S::SA, lane);
         }
+        c.finish();
         if (S::NO == 1 && kh > 0)
 #pragma unroll
           for (int m = 0; m < S::MT; ++m)
             red()[(((kh - 1) * n.nn3 + nb3) * S::MT + m) * 64 + lane] =
-                acc[o][m][0];
+                c.v[m][0];
       }
+#pragma unroll
+      for (int m = 0; m < S::MT; ++m) acc[o][m][0] = c.v[m][0];
     }
     start1();
     if (S::NO == 1 && n.ks > 1) __syncthreads();
