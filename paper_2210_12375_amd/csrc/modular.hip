@@ -1869,117 +1869,100 @@ __global__ void copy_r(R* dst, const R* src, long n) {
 // C[m][n] += sum_k Tin[k][m] Tg[k][n] over the k range of this split, added
 // into slot[split] (one owner per entry, so the sum is deterministic).  The
 // augmented C = [W; b] of the three layers, concatenated, is dtheta.  Tape
-// rows are M (inputs) and N (cotangents) wide.  blockIdx.y selects one of
+// rows are M (inputs) and N (cotangents) wide.  grid y selects one of
 // several independent products of the same shape (the stages of an attempt):
 // its tapes and slots start sin, sg and sslot elements further on.
-template <typename R>
-__global__ __launch_bounds__(256) void grad_gemm(const R* Tin, const R* Tg,
-                                                 long K, int M, int N, int S,
-                                                 R* slots, long P, long off,
-                                                 long sin, long sg,
-                                                 long sslot) {
-  constexpr int TM = 64, TN = 64, TK = 16;
-  Tin += blockIdx.y * sin;
-  Tg += blockIdx.y * sg;
-  slots += blockIdx.y * sslot;
-  __shared__ R As[TK][TM + 4];
-  __shared__ R Bs[TK][TN + 4];
-  const int tiles_n = (N + TN - 1) / TN;
-  const int tile = blockIdx.x / S, split = blockIdx.x % S;
-  const int m0 = (tile / tiles_n) * TM, n0 = (tile % tiles_n) * TN;
-  const long kc = ((K + S - 1) / S + TK - 1) / TK * TK;
-  const long k0 = split * kc, k1 = k0 + kc < K ? k0 + kc : K;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  R acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = R(0);
-  for (long kk = k0; kk < k1; kk += TK) {
-    for (int e = threadIdx.x; e < TK * TM; e += 256) {
-      const int kl = e / TM, c = e % TM;
-      const long k = kk + kl;
-      const int m = m0 + c, n = n0 + c;
-      As[kl][c] = (m < M && k < k1) ? Tin[k * M + m] : R(0);
-      Bs[kl][c] = (n < N && k < k1) ? Tg[k * N + n] : R(0);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kl = 0; kl < TK; ++kl) {
-      R a[4], bb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        a[i] = As[kl][ty * 4 + i];
-        bb[i] = Bs[kl][tx * 4 + i];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * bb[j];
-    }
-    __syncthreads();
+
+// Tile and k-split of workgroup bx out of tiles x S.  Workgroups go to the
+// eight XCDs in turn; those that read the same tape rows (one split, all
+// tiles) get indices 8 apart, so the rows come through one L2.
+__device__ __forceinline__ void tile_split(int bx, int tiles, int S, int& tile,
+                                           int& split) {
+  const int full = S / 8 * 8;
+  if (bx < full * tiles) {
+    tile = (bx >> 3) % tiles;
+    split = (bx >> 3) / tiles * 8 + (bx & 7);
+  } else {
+    const int r = bx - full * tiles;
+    tile = r % tiles;
+    split = full + r / tiles;
   }
-  R* slot = slots + (long)split * P + off;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-      if (m < M && n < N) slot[(long)m * N + n] += acc[i][j];
-    }
 }
 
-// FP32 tapes: the same product on the FP32 matrix cores
-// (v_mfma_f32_16x16x4_f32: exact FP32 products, FP32 accumulation).  Four
+// On the matrix cores of the tape's type (v_mfma_f32_16x16x4_f32,
+// v_mfma_f64_16x16x4_f64: exact products, accumulation in the type).  Four
 // wavefronts in a 2 x 2 grid, each WM x WN 16x16 tiles, so a workgroup
 // covers (32 WM) x (32 WN) of C: 128 x 128 for the square layers, 32 x 128
 // or 128 x 32 where the layer has few inputs or outputs.  Both operands
 // pass through LDS 16 tape rows at a time (contiguous runs of features).
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x4_t __attribute__((ext_vector_type(4)));
 
-// Workgroup bx of the product (tile bx / S, k-split bx % S); As, Bs: LDS of
-// at least 16 (32 WM + 16) and 16 (32 WN + 16) floats.
-template <int WM, int WN>
-__device__ __forceinline__ void grad_gemm_tile(int bx, const float* Tin,
-                                               const float* Tg, long K, int M,
-                                               int N, int S, float* slots,
-                                               long P, long off, float* As,
-                                               float* Bs) {
+// The 16x16x4 product of a type; element v of lane l's result is row
+// row(l / 16, v), column l % 16.
+template <typename R>
+struct Mm4;
+template <>
+struct Mm4<float> {
+  typedef f32x4_t V;
+  __device__ static __forceinline__ V mul(float a, float b, V c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  __device__ static __forceinline__ int row(int q, int v) { return 4 * q + v; }
+};
+template <>
+struct Mm4<double> {
+  typedef f64x4_t V;
+  __device__ static __forceinline__ V mul(double a, double b, V c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  __device__ static __forceinline__ int row(int q, int v) { return 4 * v + q; }
+};
+
+// Workgroup bx of the product (tile_split); As, Bs: LDS of at least
+// 16 (32 WM + 16) and 16 (32 WN + 16) values.
+template <typename R, int WM, int WN>
+__device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
+                                               const R* Tg, long K, int M,
+                                               int N, int S, R* slots, long P,
+                                               long off, R* As, R* Bs) {
+  typedef typename Mm4<R>::V V;
   constexpr int TM = 32 * WM, TN = 32 * WN, TK = 16;
   // row pitch 16 floats past the tile: the four lane groups of an operand
   // read land 16 banks apart
   constexpr int LA = TM + 16, LB = TN + 16;
   constexpr int NA = TK * TM / 256, NB = TK * TN / 256;  // loads per thread
   const int tiles_n = (N + TN - 1) / TN;
-  const int tile = bx / S, split = bx % S;
+  int tile, split;
+  tile_split(bx, (M + TM - 1) / TM * tiles_n, S, tile, split);
   const int m0 = (tile / tiles_n) * TM, n0 = (tile % tiles_n) * TN;
   const long kc = ((K + S - 1) / S + TK - 1) / TK * TK;
   const long k0 = split * kc, k1 = k0 + kc < K ? k0 + kc : K;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * 16 * WM, wn = (wave & 1) * 16 * WN;
   const int lr = lane & 15, lk = lane >> 4;
-  f32x4_t acc[WM][WN];
+  V acc[WM][WN];
 #pragma unroll
   for (int i = 0; i < WM; ++i)
 #pragma unroll
-    for (int j = 0; j < WN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < WN; ++j) acc[i][j] = V{R(0), R(0), R(0), R(0)};
   // the next 16 tape rows are loaded into registers while the current ones
   // are multiplied
-  float ra[NA], rb[NB];
+  R ra[NA], rb[NB];
   auto fetch = [&](long kk) {
 #pragma unroll
     for (int q = 0; q < NA; ++q) {
       const int e = tid + 256 * q, kl = e / TM, c = e % TM;
       const long k = kk + kl;
       const int m = m0 + c;
-      ra[q] = (m < M && k < k1) ? Tin[k * M + m] : 0.f;
+      ra[q] = (m < M && k < k1) ? Tin[k * M + m] : R(0);
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       const int e = tid + 256 * q, kl = e / TN, c = e % TN;
       const long k = kk + kl;
       const int n = n0 + c;
-      rb[q] = (n < N && k < k1) ? Tg[k * N + n] : 0.f;
+      rb[q] = (n < N && k < k1) ? Tg[k * N + n] : R(0);
     }
   };
   if (k0 < k1) fetch(k0);
@@ -1998,7 +1981,7 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const float* Tin,
     if (kk + TK < k1) fetch(kk + TK);
 #pragma unroll
     for (int k4 = 0; k4 < TK; k4 += 4) {
-      float a[WM], b[WN];
+      R a[WM], b[WN];
 #pragma unroll
       for (int i = 0; i < WM; ++i) a[i] = As[(k4 + lk) * LA + wm + i * 16 + lr];
 #pragma unroll
@@ -2007,72 +1990,78 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const float* Tin,
       for (int i = 0; i < WM; ++i)
 #pragma unroll
         for (int j = 0; j < WN; ++j)
-          acc[i][j] =
-              __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+          acc[i][j] = Mm4<R>::mul(a[i], b[j], acc[i][j]);
     }
     __syncthreads();
   }
-  float* slot = slots + (long)split * P + off;
+  R* slot = slots + (long)split * P + off;
 #pragma unroll
   for (int i = 0; i < WM; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int m = m0 + wm + i * 16 + lk * 4 + v;
+        const int m = m0 + wm + i * 16 + Mm4<R>::row(lk, v);
         const int n = n0 + wn + j * 16 + lr;
         if (m < M && n < N) slot[(long)m * N + n] += acc[i][j][v];
       }
 }
 
-template <int WM, int WN>
+template <typename R, int WM, int WN>
 __global__ __launch_bounds__(256) void grad_gemm_mfma(
-    const float* Tin, const float* Tg, long K, int M, int N, int S,
-    float* slots, long P, long off, long sin, long sg, long sslot) {
-  __shared__ float As[16 * (32 * WM + 16)];
-  __shared__ float Bs[16 * (32 * WN + 16)];
-  grad_gemm_tile<WM, WN>(blockIdx.x, Tin + blockIdx.y * sin,
+    const R* Tin, const R* Tg, long K, int M, int N, int S, R* slots, long P,
+    long off, long sin, long sg, long sslot) {
+  __shared__ R As[16 * (32 * WM + 16)];
+  __shared__ R Bs[16 * (32 * WN + 16)];
+  grad_gemm_tile<R, WM, WN>(blockIdx.x, Tin + blockIdx.y * sin,
                          Tg + blockIdx.y * sg, K, M, N, S,
                          slots + blockIdx.y * sslot, P, off, As, Bs);
 }
 
-// Tile shapes of the FP32 matrix-core gradient products.
+// Tile shapes of the matrix-core gradient products.
 enum GemmShape { kG14, kG41, kG42, kG34, kG44 };
 
 // The products of one chunk (one per layer, different shapes) in one
 // launch: workgroups [0, nblk[0]) are product 0's, and so on, each
 // product's workgroups exactly those of its own launch.
+template <typename R>
 struct GemmGroup {
-  const float* Tin[3];
-  const float* Tg[3];
+  const R* Tin[3];
+  const R* Tg[3];
   int M[3], N[3], S[3], shape[3], nblk[3];
   long off[3];
   long K, P;
-  float* slots;
+  R* slots;
 };
 
-__global__ __launch_bounds__(256) void grad_gemm_group(GemmGroup g) {
-  __shared__ float As[16 * (128 + 16)];
-  __shared__ float Bs[16 * (128 + 16)];
+template <typename R>
+__global__ __launch_bounds__(256) void grad_gemm_group(GemmGroup<R> g) {
+  __shared__ R As[16 * (128 + 16)];
+  __shared__ R Bs[16 * (128 + 16)];
   int b = blockIdx.x, j = 0;
   while (j < 2 && b >= g.nblk[j]) b -= g.nblk[j++];
-  const float *Tin = g.Tin[j], *Tg = g.Tg[j];
+  const R *Tin = g.Tin[j], *Tg = g.Tg[j];
   const int M = g.M[j], N = g.N[j], S = g.S[j];
   switch (g.shape[j]) {
     case kG14:
-      grad_gemm_tile<1, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P, g.off[j], As, Bs);
+      grad_gemm_tile<R, 1, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                              g.off[j], As, Bs);
       break;
     case kG41:
-      grad_gemm_tile<4, 1>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P, g.off[j], As, Bs);
+      grad_gemm_tile<R, 4, 1>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                              g.off[j], As, Bs);
       break;
     case kG42:
-      grad_gemm_tile<4, 2>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P, g.off[j], As, Bs);
+      grad_gemm_tile<R, 4, 2>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                              g.off[j], As, Bs);
       break;
     case kG34:
-      grad_gemm_tile<3, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P, g.off[j], As, Bs);
+      grad_gemm_tile<R, 3, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                              g.off[j], As, Bs);
       break;
     default:
-      grad_gemm_tile<4, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P, g.off[j], As, Bs);
+      grad_gemm_tile<R, 4, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                              g.off[j], As, Bs);
   }
 }
 
@@ -2094,7 +2083,8 @@ __global__ __launch_bounds__(512) void grad_gemm_big(
   __shared__ float Bs[TK * LA];
   __shared__ float Bias[TK];
   const int tiles_n = (N + TT - 1) / TT;
-  const int tile = blockIdx.x / S, split = blockIdx.x % S;
+  int tile, split;
+  tile_split(blockIdx.x, (M + TT - 1) / TT * tiles_n, S, tile, split);
   const int m0 = (tile / tiles_n) * TT, n0 = (tile % tiles_n) * TT;
   const bool brow = m0 == 0;
   const long kc = ((K + S - 1) / S + TK - 1) / TK * TK;
@@ -2170,129 +2160,226 @@ __global__ __launch_bounds__(512) void grad_gemm_big(
 // (the top 16 bits of the exact residual x - hi), and C += Ah Bh + Ah Bl +
 // Al Bh (v_mfma_f32_16x16x32_bf16, FP32 accumulation): the dropped Al Bl
 // and the truncated residuals leave about 2^-16 of each product, far below
-// the BF16 weights' own rounding.  Tiles of 128 (m) x 256 (n) of C over 8
-// wavefronts (2 x 4, each 64 x 64 = 4 x 4 MFMA tiles); 32 tape rows a
-// stage, both operands stored in LDS k-contiguous ([m][k] and [n][k], row
-// pitch 40 halves) so that a lane's eight k values are one 16-byte read;
-// each thread loads eight rows of one feature (coalesced over features)
-// and writes its eight k values as one 16-byte store per term; the next
-// stage's rows are loaded during the products.  C rows are all M input
-// features (the bias feature included), as in grad_gemm_mfma.
-constexpr int kBgM = 128, kBgN = 256, kBgK = 32, kBgP = kBgK + 8;
+// the BF16 weights' own rounding.  Tiles of TM (m) x 256 (n) of C over 8
+// wavefronts (each 64 x 128 for TM = 256, 64 x 64 for TM = 128); 32 tape
+// rows a stage, double-buffered: the next stage is loaded (one feature and
+// eight rows a thread, coalesced over features; the row offset is uniform,
+// so a buffer load takes it from a scalar register) and split while this
+// one is multiplied.  LDS holds both operands k-contiguous, 64 bytes a
+// feature, its four 16-byte chunks exchanged by the feature's index so that
+// the reads of a product and the stores meet no bank conflict.  The bias row
+// of C (input feature M - 1) is summed by the tiles of the first rows, from
+// the cotangents they stage, on plain FMAs: as a 513th row of matrix tiles
+// it cost a fifth of the launch.
+// K = 114,688 rows of 513 x 512 (the step of an 8192-instance CNF): 498 us
+// before (128 x 256 tiles, one buffer, tiles of a split far apart), 234 now.
+constexpr int kBgN = 256, kBgK = 32;
+constexpr int kBgRound = 256;  // workgroups of a launch: one a compute unit
+
+// 32-row stage of an operand: the 16-byte chunk c (k = 8 c ..) of feature f.
+__device__ __forceinline__ int bg_slot(int f, int c) {
+  return f * kBgK + ((c ^ (f >> 1)) & 3) * 8;
+}
 
 __device__ __forceinline__ void split_store8(uint16_t* hi, uint16_t* lo,
                                              const float (&v)[8]) {
   uint32_t h[4], l[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    uint32_t w[2], r[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const uint32_t u = __float_as_uint(v[2 * j + q]);
-      const float res = v[2 * j + q] - __uint_as_float(u & 0xffff0000u);
-      w[q] = u >> 16;
-      r[q] = __float_as_uint(res) >> 16;
-    }
-    h[j] = w[0] | (w[1] << 16);
-    l[j] = r[0] | (r[1] << 16);
+    const uint32_t u0 = __float_as_uint(v[2 * j]);
+    const uint32_t u1 = __float_as_uint(v[2 * j + 1]);
+    const float r0 = v[2 * j] - __uint_as_float(u0 & 0xffff0000u);
+    const float r1 = v[2 * j + 1] - __uint_as_float(u1 & 0xffff0000u);
+    // the top halves of two values in one register
+    h[j] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+    l[j] = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0),
+                                 0x07060302u);
   }
   *reinterpret_cast<uint4*>(hi) = make_uint4(h[0], h[1], h[2], h[3]);
   *reinterpret_cast<uint4*>(lo) = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
-__global__ __launch_bounds__(512) void grad_gemm_bf16(
+template <int TM>
+constexpr size_t bg_lds() {
+  return sizeof(uint16_t) * 2 * 2 * (TM + kBgN) * kBgK;
+}
+
+template <int TM>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+void grad_gemm_bf16(
     const float* Tin, const float* Tg, long K, int M, int N, int S,
     float* slots, long P, long off) {
-  __shared__ __align__(16) uint16_t Ah[kBgM * kBgP];
-  __shared__ __align__(16) uint16_t Al[kBgM * kBgP];
-  __shared__ __align__(16) uint16_t Bh[kBgN * kBgP];
-  __shared__ __align__(16) uint16_t Bl[kBgN * kBgP];
-  const int tiles_n = (N + kBgN - 1) / kBgN;
-  const int tile = blockIdx.x / S, split = blockIdx.x % S;
-  const int m0 = (tile / tiles_n) * kBgM, n0 = (tile % tiles_n) * kBgN;
+  constexpr int NJ = TM == 256 ? 8 : 4;          // 16-column tiles of a wave
+  constexpr int GA = TM * 4 / 512, SA = 512 / TM;  // chunks a thread, stride
+  constexpr int kBuf = 2 * (TM + kBgN) * kBgK;     // halves of a buffer
+  constexpr int oAl = TM * kBgK, oBh = 2 * oAl, oBl = oBh + kBgN * kBgK;
+  extern __shared__ __align__(16) uint16_t bg_mem[];
+  const int tiles_n = (N + kBgN - 1) / kBgN, Mw = M - 1;
+  int tile, split;
+  tile_split(blockIdx.x, (Mw + TM - 1) / TM * tiles_n, S, tile, split);
+  const int m0 = (tile / tiles_n) * TM, n0 = (tile % tiles_n) * kBgN;
+  const bool brow = m0 == 0;
   const long kc = ((K + S - 1) / S + kBgK - 1) / kBgK * kBgK;
-  const long k0 = split * kc, k1 = k0 + kc < K ? k0 + kc : K;
+  const long k0 = split * kc;
+  // (kc M and kc N floats stay below 2^31 bytes: launch_grad_gemm)
+  const int nk = k0 < K ? (int)(K - k0 < kc ? K - k0 : kc) : 0;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 2) * 64, wn = (wave & 3) * 64;
-  const int r = lane & 15, kq = (lane >> 4) * 8;
-  // staging: A feature tid % 128, k group tid / 128 (eight rows); B features
-  // tid % 256 and the k groups tid / 256 and tid / 256 + 2
-  const int am = tid % kBgM, ag = tid / kBgM;
-  const int bn = tid % kBgN, bg = tid / kBgN;
-  float ra[8], rb[2][8];
-  auto fetch = [&](long kk) {
+  const int wm = TM == 256 ? (wave >> 1) * 64 : (wave >> 2) * 64;
+  const int wn = TM == 256 ? (wave & 1) * 128 : (wave & 3) * 64;
+  const int r = lane & 15, kq = lane >> 4;
+  const auto bufA = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(Tin) + (nk > 0 ? k0 * M : 0), 0, nk * M * 4,
+      0x00027000);
+  const auto bufB = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<float*>(Tg) + (nk > 0 ? k0 * N : 0), 0, nk * N * 4,
+      0x00027000);
+  const int fa = tid % TM, fb = tid % kBgN;
+  const int ga = __builtin_amdgcn_readfirstlane(tid / TM);
+  const int gb = __builtin_amdgcn_readfirstlane(tid / kBgN);
+  // (a feature past the last gives rows or columns of C that nobody stores)
+  const int va = min(m0 + fa, Mw - 1) * 4, vb = min(n0 + fb, N - 1) * 4;
+  float ra[GA][8], rb[2][8], rz = 0.f;
+  auto load = [](auto buf, int v, int s) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, v, s, 0));
+  };
+  auto fetch = [&](int kk) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const long k = kk + ag * 8 + j;
-      const int m = m0 + am;
-      ra[j] = (m < M && k < k1) ? Tin[k * M + m] : 0.f;
-    }
+    for (int q = 0; q < GA; ++q)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = min(kk + (ga + SA * q) * 8 + j, nk - 1);
+        ra[q][j] = load(bufA, va, k * M * 4);
+      }
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const long k = kk + (bg + 2 * q) * 8 + j;
-        const int n = n0 + bn;
-        rb[q][j] = (n < N && k < k1) ? Tg[k * N + n] : 0.f;
+        const int k = min(kk + (gb + 2 * q) * 8 + j, nk - 1);
+        rb[q][j] = load(bufB, vb, k * N * 4);
       }
+    if (brow) {  // lane 8 q + j: the bias feature of row j of chunk q
+      const int k = kk + (gb + 2 * (lane >> 3 & 1)) * 8 + (lane & 7);
+      rz = load(bufA, min(k, nk - 1) * M * 4 + Mw * 4, 0);
+    }
   };
-  f32x4 acc[4][4];
+  float bias = 0.f;
+  auto stage = [&](uint16_t* b, int kk) {
+    if (kk + kBgK > nk) {  // rows past the split's last are zeros
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+#pragma unroll
+        for (int q = 0; q < GA; ++q)
+          if (kk + (ga + SA * q) * 8 + j >= nk) ra[q][j] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          if (kk + (gb + 2 * q) * 8 + j >= nk) rb[q][j] = 0.f;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < GA; ++q) {
+      const int o = bg_slot(fa, ga + SA * q);
+      split_store8(b + o, b + oAl + o, ra[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int o = bg_slot(fb, gb + 2 * q);
+      split_store8(b + oBh + o, b + oBl + o, rb[q]);
+    }
+    if (brow)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          bias = fmaf(__uint_as_float(__builtin_amdgcn_readlane(
+                          __float_as_uint(rz), 8 * q + j)),
+                      rb[q][j], bias);
+  };
+  f32x4 acc[4][NJ];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (k0 < k1) fetch(k0);
-  for (long kk = k0; kk < k1; kk += kBgK) {
-    split_store8(Ah + am * kBgP + ag * 8, Al + am * kBgP + ag * 8, ra);
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-      split_store8(Bh + bn * kBgP + (bg + 2 * q) * 8,
-                   Bl + bn * kBgP + (bg + 2 * q) * 8, rb[q]);
-    __syncthreads();
-    if (kk + kBgK < k1) fetch(kk + kBgK);
-    bf16x8 ah[4], al[4], bh[4], bl[4];
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (nk > 0) {
+    fetch(0);
+    stage(bg_mem, 0);
+  }
+  __syncthreads();
+  int cur = 0;
+  for (int kk = 0; kk < nk; kk += kBgK) {
+    const bool more = kk + kBgK < nk;
+    if (more) fetch(kk + kBgK);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint16_t* b = bg_mem + cur * kBuf;
+    bf16x8 ah[4], al[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int o = (wm + i * 16 + r) * kBgP + kq;
-      ah[i] = mtile::lds8(Ah + o);
-      al[i] = mtile::lds8(Al + o);
+      const int o = bg_slot(wm + i * 16 + r, kq);
+      ah[i] = mtile::lds8(b + o);
+      al[i] = mtile::lds8(b + oAl + o);
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int o = (wn + j * 16 + r) * kBgP + kq;
-      bh[j] = mtile::lds8(Bh + o);
-      bl[j] = mtile::lds8(Bl + o);
+    for (int j = 0; j < NJ; ++j) {
+      const int o = bg_slot(wn + j * 16 + r, kq);
+      const bf16x8 bh = mtile::lds8(b + oBh + o);
+      const bf16x8 bl = mtile::lds8(b + oBl + o);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i][j] = mtile::mfma(ah[i], bh, acc[i][j]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i][j] = mtile::mfma(ah[i], bl, acc[i][j]);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i][j] = mtile::mfma(al[i], bh, acc[i][j]);
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        acc[i][j] = mtile::mfma(ah[i], bh[j], acc[i][j]);
-        acc[i][j] = mtile::mfma(ah[i], bl[j], acc[i][j]);
-        acc[i][j] = mtile::mfma(al[i], bh[j], acc[i][j]);
-      }
+    cur ^= 1;
+    __builtin_amdgcn_sched_barrier(0);
+    if (more) stage(bg_mem + cur * kBuf, kk + kBgK);
     __syncthreads();
   }
   float* slot = slots + (long)split * P + off;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int m = m0 + wm + i * 16 + (lane >> 4) * 4 + v;
+        const int m = m0 + wm + i * 16 + kq * 4 + v;
         const int n = n0 + wn + j * 16 + r;
-        if (m < M && n < N) slot[(long)m * N + n] += acc[i][j][v];
+        if (m < Mw && n < N) slot[(long)m * N + n] += acc[i][j][v];
       }
+  if (brow) {  // the two threads of a feature summed half of the rows each
+    float* part = reinterpret_cast<float*>(bg_mem);
+    if (tid >= kBgN) part[fb] = bias;
+    __syncthreads();
+    if (tid < kBgN && n0 + fb < N)
+      slot[(long)Mw * N + n0 + fb] += bias + part[fb];
+  }
+}
+
+// k-splits of a product on `tiles` tiles, `round` of them wanted: at least
+// 256 tape rows each, or 64 while the launch would leave compute units idle
+// (a split costs its slot's tile read and written once; a short tape costs
+// the chain of its stages).  The three
+// products of 4200 rows of a 7->50->50->6 field: 16 splits 40 us, 65 21; of
+// 3500 FP64 rows of 17->96->96->16 (on FMA, three launches) 195 -> 39 us.
+constexpr long kMinSplit = 64;
+// Products that run beside the cotangent chain of a small batch leave it the
+// compute units it needs (its workgroups fill one each, and one that finds
+// none waits for a product's to end): wgs is the most workgroups they take.
+// 1024 instances of 65->256->256->64, step VJP 58 us beside 256, 48 beside 128.
+constexpr int kAllWgs = 1 << 20;
+inline int k_splits(long K, long tiles, long round, int S) {
+  const long most = std::max<long>(
+      K / 256, std::min<long>(K / kMinSplit, (256 + tiles - 1) / tiles));
+  return (int)std::max<long>(
+      1, std::min<long>(std::min<long>(most, S), (round + tiles - 1) / tiles));
 }
 
 // Launch shape of a parameter-gradient product C[M, N] = sum over K tape
-// rows: tile shape (FP32 matrix cores: 32 WM x 32 WN), narrow where the
-// layer has few inputs or outputs, so little of a tile is padding (a
+// rows: tile shape (32 WM x 32 WN), narrow where the layer has few inputs or
+// outputs, so little of a tile is padding (a
 // 257 x 64 layer on 128 x 64 tiles, 66 x 256 on 96 x 128); k-splits: a few
 // rounds of workgroups over the chip (about 2048 over all nb products, so
-// the last round's tail is short), each split at least 256 tape rows long,
-// at most the S slots there are.  big: 256 x 256 tiles (layers with at
+// the last round's tail is short), each split long enough
+// (k_splits), at most the S slots there are.  big: 256 x 256 tiles (layers with at
 // least 256 weight rows and columns and long tapes).
 struct GemmPlan {
   int shape, tiles, splits;
@@ -2301,7 +2388,7 @@ struct GemmPlan {
 };
 
 inline GemmPlan plan_grad_gemm(bool f32, long K, int M, int N, int S,
-                               int nb) {
+                               int nb, int wgs = kAllWgs) {
   GemmPlan p{};
   int wm = 4, wn = 4;
   p.shape = kG44;
@@ -2309,24 +2396,60 @@ inline GemmPlan plan_grad_gemm(bool f32, long K, int M, int N, int S,
   else if (N <= 32) wn = 1, p.shape = kG41;
   else if (N <= 64 && M > 64) wn = 2, p.shape = kG42;
   else if (M <= 96 && N > 64) wm = 3, p.shape = kG34;
-  const int tm = !f32 ? 64 : 32 * wm, tn = !f32 ? 64 : 32 * wn;
+  const int tm = 32 * wm, tn = 32 * wn;
   p.tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
-  int splits = (2048 + p.tiles * nb - 1) / (p.tiles * nb);
-  const long by_k = K / 256 > 0 ? K / 256 : 1;
-  if (splits > by_k) splits = (int)by_k;
-  if (splits > S) splits = S;
-  p.splits = splits;
+  p.splits = k_splits(K, (long)p.tiles * nb, std::min(wgs, 2048), S);
   p.big = f32 && M - 1 >= 256 && N >= 256 && K * nb >= 65536;
   if (p.big) {
     // weight rows on 256 x 256 tiles; the bias row is the last input
     // feature and rides with the first row of tiles
     p.tb = ((M - 1 + 255) / 256) * ((N + 255) / 256);
-    int sb = (1024 + p.tb * nb - 1) / (p.tb * nb);
-    if (sb > by_k) sb = (int)by_k;
-    if (sb > S) sb = S;
-    p.sb = sb;
+    p.sb = k_splits(K, (long)p.tb * nb, std::min(wgs, 1024), S);
   }
   return p;
+}
+
+// Split-BF16 products: 256 x 256 tiles where a round of splits over them
+// fills the chip, 128 x 256 below (half the splits' rows a workgroup).
+struct BgPlan {
+  int tm, tiles, splits;
+};
+
+inline BgPlan plan_bf16(long K, int M, int N, int S, int wgs = kAllWgs) {
+  BgPlan p{};
+  for (p.tm = 256;; p.tm = 128) {
+    p.tiles = (M - 1 + p.tm - 1) / p.tm * ((N + kBgN - 1) / kBgN);
+    p.splits = k_splits(K, p.tiles, std::min(wgs, kBgRound), S);
+    if (p.tm == 128 || (p.tiles * p.splits >= 256 && K / p.splits >= 512))
+      return p;
+  }
+}
+
+// Most slots any of a chunk's three products uses (shorter chunks use fewer).
+inline int grad_slots(bool f32, bool bf16, long K, const int M[3],
+                      const int N[3], int S) {
+  int g = 1;
+  for (int j = 0; j < 3; ++j) {
+    const GemmPlan p = plan_grad_gemm(f32, K, M[j], N[j], S, 1);
+    g = std::max(g, p.big ? std::max(p.splits, p.sb) : p.splits);
+    if (bf16 && M[j] > 256 && N[j] >= 256)
+      g = std::max(g, plan_bf16(K, M[j], N[j], S).splits);
+  }
+  return g;
+}
+
+template <int TM>
+hipError_t launch_bf16(const BgPlan& p, const float* Tin, const float* Tg,
+                       long K, int M, int N, float* slots, long P, long off,
+                       hipStream_t s) {
+  const hipError_t e = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(grad_gemm_bf16<TM>),
+      hipFuncAttributeMaxDynamicSharedMemorySize, (int)bg_lds<TM>());
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(grad_gemm_bf16<TM>, dim3(p.tiles * p.splits), dim3(512),
+                     bg_lds<TM>(), s, Tin, Tg, K, M, N, p.splits, slots, P,
+                     off);
+  return hipGetLastError();
 }
 
 // nb > 1: nb products of the same shape in one launch (grid y), product j
@@ -2337,23 +2460,22 @@ template <typename R>
 hipError_t launch_grad_gemm(const R* Tin, const R* Tg, long K, int M, int N,
                             int S, R* slots, long P, long off, hipStream_t s,
                             int nb = 1, long sin = 0, long sg = 0,
-                            long sslot = 0, bool bf16 = false) {
+                            long sslot = 0, bool bf16 = false,
+                            int wgs = kAllWgs) {
   if (nb < 1 || (nb > 1 && sslot < (long)S * P)) return hipErrorInvalidValue;
   const bool f32 = std::is_same<R, float>::value;
-  const GemmPlan pl = plan_grad_gemm(f32, K, M, N, S, nb);
+  const GemmPlan pl = plan_grad_gemm(f32, K, M, N, S, nb, wgs);
   const dim3 g(pl.tiles * pl.splits, nb), blk(256);
   const int splits = pl.splits;
   if constexpr (std::is_same<R, float>::value) {
     if (bf16 && nb == 1 && M - 1 >= 256 && N >= 256) {
-      // 128 x 256 tiles over all M features, about 1024 workgroups
-      const int tb = ((M + kBgM - 1) / kBgM) * ((N + kBgN - 1) / kBgN);
-      const long by_k = K / 256 > 0 ? K / 256 : 1;
-      int sb = (1024 + tb - 1) / tb;
-      if (sb > by_k) sb = (int)by_k;
-      if (sb > S) sb = S;
-      hipLaunchKernelGGL(grad_gemm_bf16, dim3(tb * sb), dim3(512), 0, s, Tin,
-                         Tg, K, M, N, sb, slots, P, off);
-      return hipGetLastError();
+      const BgPlan p = plan_bf16(K, M, N, S, wgs);
+      const long kc = (K + p.splits - 1) / p.splits + kBgK;
+      if (kc * std::max(M, N) * 4 < (1L << 31))  // the kernel's row offsets
+        return p.tm == 256 ? launch_bf16<256>(p, Tin, Tg, K, M, N, slots, P,
+                                              off, s)
+                           : launch_bf16<128>(p, Tin, Tg, K, M, N, slots, P,
+                                              off, s);
     }
     if (pl.big) {
       hipLaunchKernelGGL(grad_gemm_big, dim3(pl.tb * pl.sb, nb), dim3(512), 0,
@@ -2361,49 +2483,49 @@ hipError_t launch_grad_gemm(const R* Tin, const R* Tg, long K, int M, int N,
                          sg, sslot);
       return hipGetLastError();
     }
-    switch (pl.shape) {
-      case kG14:
-        hipLaunchKernelGGL((grad_gemm_mfma<1, 4>), g, blk, 0, s, Tin, Tg, K,
-                           M, N, splits, slots, P, off, sin, sg, sslot);
-        break;
-      case kG41:
-        hipLaunchKernelGGL((grad_gemm_mfma<4, 1>), g, blk, 0, s, Tin, Tg, K,
-                           M, N, splits, slots, P, off, sin, sg, sslot);
-        break;
-      case kG42:
-        hipLaunchKernelGGL((grad_gemm_mfma<4, 2>), g, blk, 0, s, Tin, Tg, K,
-                           M, N, splits, slots, P, off, sin, sg, sslot);
-        break;
-      case kG34:
-        hipLaunchKernelGGL((grad_gemm_mfma<3, 4>), g, blk, 0, s, Tin, Tg, K,
-                           M, N, splits, slots, P, off, sin, sg, sslot);
-        break;
-      default:
-        hipLaunchKernelGGL((grad_gemm_mfma<4, 4>), g, blk, 0, s, Tin, Tg, K,
-                           M, N, splits, slots, P, off, sin, sg, sslot);
-    }
-  } else {
-    hipLaunchKernelGGL(grad_gemm<R>, g, blk, 0, s, Tin, Tg, K, M, N, splits,
-                       slots, P, off, sin, sg, sslot);
+  }
+  switch (pl.shape) {
+    case kG14:
+      hipLaunchKernelGGL((grad_gemm_mfma<R, 1, 4>), g, blk, 0, s, Tin, Tg, K,
+                         M, N, splits, slots, P, off, sin, sg, sslot);
+      break;
+    case kG41:
+      hipLaunchKernelGGL((grad_gemm_mfma<R, 4, 1>), g, blk, 0, s, Tin, Tg, K,
+                         M, N, splits, slots, P, off, sin, sg, sslot);
+      break;
+    case kG42:
+      hipLaunchKernelGGL((grad_gemm_mfma<R, 4, 2>), g, blk, 0, s, Tin, Tg, K,
+                         M, N, splits, slots, P, off, sin, sg, sslot);
+      break;
+    case kG34:
+      hipLaunchKernelGGL((grad_gemm_mfma<R, 3, 4>), g, blk, 0, s, Tin, Tg, K,
+                         M, N, splits, slots, P, off, sin, sg, sslot);
+      break;
+    default:
+      hipLaunchKernelGGL((grad_gemm_mfma<R, 4, 4>), g, blk, 0, s, Tin, Tg, K,
+                         M, N, splits, slots, P, off, sin, sg, sslot);
   }
   return hipGetLastError();
 }
 
-// The three layers' products of one chunk (tape rows K): grouped, one
-// launch of grad_gemm_group where none takes the 256 x 256 tiles (each product with
-// exactly the workgroups and k-splits of its own launch, so the slots hold
-// the same sums), else one launch each.
+// The three layers' products of one chunk (tape rows K) in one launch where
+// none takes the 256 x 256 tiles; one launch each there, and for BF16 tapes
+// unless grouped (the last chunk, with nothing beside it: one launch 48 us,
+// three 88; in the others the split-BF16 product is worth its launch).
 template <typename R>
 hipError_t launch_grad_gemm3(const R* const Tin[3], const R* const Tg[3],
                              long K, const int M[3], const int N[3], int S,
                              R* slots, long P, const long off[3],
-                             hipStream_t s, bool grouped, bool bf16) {
-  if constexpr (std::is_same<R, float>::value) {
-    GemmGroup g{};
+                             hipStream_t s, bool grouped, bool bf16,
+                             int wgs) {
+  if (grouped || !bf16) {
+    GemmGroup<R> g{};
     bool ok = true;
     long nblk = 0;
     for (int j = 0; j < 3; ++j) {
-      const GemmPlan pl = plan_grad_gemm(true, K, M[j], N[j], S, 1);
+      const GemmPlan pl =
+          plan_grad_gemm(std::is_same<R, float>::value, K, M[j], N[j], S, 1,
+                         wgs == kAllWgs ? wgs : wgs / 3);
       ok = ok && !pl.big;
       g.Tin[j] = Tin[j];
       g.Tg[j] = Tg[j];
@@ -2415,11 +2537,11 @@ hipError_t launch_grad_gemm3(const R* const Tin[3], const R* const Tg[3],
       g.off[j] = off[j];
       nblk += g.nblk[j];
     }
-    if (ok && grouped) {
+    if (ok) {
       g.K = K;
       g.P = P;
       g.slots = slots;
-      hipLaunchKernelGGL(grad_gemm_group, dim3((unsigned)nblk), dim3(256), 0,
+      hipLaunchKernelGGL(grad_gemm_group<R>, dim3((unsigned)nblk), dim3(256), 0,
                          s, g);
       return hipGetLastError();
     }
@@ -2427,7 +2549,7 @@ hipError_t launch_grad_gemm3(const R* const Tin[3], const R* const Tg[3],
   hipError_t e = hipSuccess;
   for (int j = 0; j < 3 && e == hipSuccess; ++j)
     e = launch_grad_gemm<R>(Tin[j], Tg[j], K, M[j], N[j], S, slots, P, off[j],
-                            s, 1, 0, 0, 0, bf16);
+                            s, 1, 0, 0, 0, bf16, wgs);
   return e;
 }
 
@@ -2440,7 +2562,15 @@ __global__ void reduce_slots(const R* slots, int G, long P, R* out) {
   slots += blockIdx.y * (long)G * P;
   out += blockIdx.y * P;
   R acc = R(0);
-  for (int g = 0; g < G; ++g) acc += slots[(long)g * P + p];
+  int g = 0;
+  for (; g + 16 <= G; g += 16) {  // 16 loads in flight, added in order
+    R v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = slots[(long)(g + j) * P + p];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) acc += v[j];
+  }
+  for (; g < G; ++g) acc += slots[(long)g * P + p];
   out[p] = acc;
 }
 
@@ -2579,12 +2709,15 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
   // Every GEMM adds into the slots on that one stream, in chunk order.
   const bool ovl = mat && b.C >= 2 && nmax > 1;
   const int Cc = ovl ? b.C / 2 : b.C;
-  // k-split slots: a GEMM over K tape rows uses at most K / 256 of them, so
-  // only those of the largest chunk are cleared and summed
-  const long Bs7 = 7L * (m.cnf ? 2 : 1) * m.B;
-  const int G = (int)std::min<long>(b.G, std::max<long>(1, Cc * Bs7 / 256));
-  hipLaunchKernelGGL(fill_r<R>, lin_grid((long)G * b.P), blk, 0, s, b.slots,
-                     (long)G * b.P, R(0));
+  // k-split slots: only those the products of the largest chunk use are
+  // cleared and summed
+  const bool bf16 = im.mw.packed != nullptr && !im.mw.f32;
+  const int gm[3] = {m.d_in + 2, m.H + 1, m.H + 1}, gn[3] = {m.H, m.H, m.d_in};
+  const int G = grad_slots(std::is_same<R, float>::value, bf16,
+                           Cc * 7L * (m.cnf ? 2 : 1) * m.B, gm, gn, b.G);
+  // (the chain's launch and the recomputation's: a unit a tile each)
+  const long busy = 2 * ((m.B + (m.cnf ? 7 : 15)) / (m.cnf ? 8 : 16));
+  const int wgs = ovl && busy <= 192 ? (int)(256 - busy) : kAllWgs;
   hipStream_t s3 = nullptr;
   if (ovl) {
     if (im.ev[0] == nullptr)
@@ -2592,8 +2725,13 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
         if (e == hipSuccess && ev == nullptr)
           e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e == hipSuccess) e = shared_aux_stream2(&s3);
+    if (e == hipSuccess) e = hipEventRecord(im.ev[6], s);
+    if (e == hipSuccess) e = hipStreamWaitEvent(s3, im.ev[6], 0);
     if (e != hipSuccess) return e;
   }
+  // (on the products' stream: beside the first steps)
+  hipLaunchKernelGGL(fill_r<R>, lin_grid((long)G * b.P), blk, 0,
+                     ovl ? s3 : s, b.slots, (long)G * b.P, R(0));
   auto back_step = [&](int n, const R* Yh, const R* Ah, int j,
                        int setup) -> hipError_t {
     // this step's place in its tape chunk (steps are taken in reverse)
@@ -2712,12 +2850,11 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
                                 b.T3in + r0 * (H + 1)};
         const R* const tg[3] = {b.T1g + r0 * H, b.T2g + r0 * H,
                                 b.T3g + r0 * din};
-        const int gm[3] = {n0 + 1, H + 1, H + 1}, gn[3] = {H, H, din};
         const long go[3] = {0, o2, o3};
         // (the last chunk's products, which nothing runs beside, in one
         // launch; the others one layer at a time, beside the VJPs)
         r = launch_grad_gemm3<R>(ti, tg, Kc, gm, gn, G, b.slots, b.P, go, sg,
-                                 n == 0, im.mw.packed != nullptr && !im.mw.f32);
+                                 n == 0, bf16, n == 0 ? kAllWgs : wgs);
       }
       if (r == hipSuccess && ovl) r = hipEventRecord(im.ev[7 + half], s3);
       if (r != hipSuccess) return r;
