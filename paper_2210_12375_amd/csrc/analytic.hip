@@ -18,6 +18,7 @@
 // the register allocation its own state needs.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -73,6 +74,47 @@ __host__ __device__ constexpr bool dense_uses(int j) {
   return M::P[j][0] != 0.0 || M::P[j][1] != 0.0 || M::P[j][2] != 0.0 ||
          M::P[j][3] != 0.0;
 }
+
+// FP64 Van der Pol instances take two neighbouring lanes each, which compute
+// the same thing but for one call: the powers of the error and of the
+// previous error, 226 instructions each of the ~1000 that a wavefront issues
+// for an attempt (one every four cycles, whatever its lanes do), are taken
+// by one lane each.
+template <typename R, class F>
+constexpr int kLanes = std::is_same<R, double>::value && F::N == 2 ? 2 : 1;
+
+// The other lane's value.
+__device__ __forceinline__ double swap_pair(double x) {
+  const long long u = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_mov_dpp((int)u, 0xB1, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), 0xB1, 0xF, 0xF, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// The tableau, held in registers beside the small fields: an FP64 constant
+// costs two moves each time it is used (176 of those 1000 instructions).
+// Together, 5003 FP64 instances (half of them Van der Pol, one of 1401
+// attempts) 2083 -> 1670 us, 64 of up to 204 attempts 418 -> 294; with the
+// branch-free commit below 1296 and 262, FP32 65,536 instances 1187 -> 1008.
+template <typename R, class M, bool HOLD>
+struct Consts {
+  R A[7][7], E[7];
+  __device__ __forceinline__ static void hold(R& x) {
+    if constexpr (HOLD) asm volatile("" : "+v"(x));
+  }
+  __device__ __forceinline__ Consts() {
+#pragma unroll
+    for (int s = 0; s < 7; ++s) {
+#pragma unroll
+      for (int j = 0; j < 7; ++j) {
+        A[s][j] = R(M::A[s][j]);
+        if (M::A[s][j] != 0.0) hold(A[s][j]);
+      }
+      E[s] = R(M::E[s]);
+      if (M::E[s] != 0.0) hold(E[s]);
+    }
+  }
+};
 
 // ---- one lane's instance -----------------------------------------------------
 
@@ -196,17 +238,18 @@ __device__ __forceinline__ void finish_lane(const AnalyticArgs<R>& a,
 // One attempted step of one instance (accept or reject), in the order of the
 // reference algorithm: stages, error norm, controller, dense output, commit.
 // REC: write the attempt record; KEEP: keep the interpolant for solver_eval.
-// The controller is branch-free (selects); only the rare paths (dense output,
-// the step limit) branch.
+// Controller and commit are branch-free (selects), a taken branch costs a lone
+// wavefront several instructions; only the dense output branches.  n_att: this
+// attempt's number.
 template <typename R, class M, class F, bool REC, bool KEEP, int TW>
 __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
-                                        Lane<R, F::N, TW>& L, const F& f) {
+                                        Lane<R, F::N, TW>& L, const F& f,
+                                        const Consts<R, M, F::N == 2>& K,
+                                        [[maybe_unused]] int n_att) {
   constexpr int N = F::N;
-  if (__builtin_expect(L.n_att >= a.ctrl.max_steps, 0)) {
-    L.status = kMaxSteps;
-    return;
-  }
-  const bool last = L.t + double(L.h) >= L.te;
+  const double tsum = L.t + double(L.h);
+  const bool last = tsum >= L.te;
+  const double tnew = last ? L.te : tsum;
   const R hs = last ? R(L.te - L.t) : L.h;
 
   // Stages 2..7: Y_s = y + h sum_{j<s} a_sj k_j, k_s = f(t + c_s h, Y_s).
@@ -222,7 +265,7 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
       R acc = R(0);
 #pragma unroll
       for (int j = 0; j < s; ++j)
-        if (M::A[s][j] != 0.0) acc += R(M::A[s][j]) * L.k[j][q];
+        if (M::A[s][j] != 0.0) acc += K.A[s][j] * L.k[j][q];
       if (kCompensated<R> && s == 6) {
         const R inc = hs * acc + L.yc[q];
         const R sum = L.y[q] + inc;
@@ -236,8 +279,6 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
     }
     f(Y, L.k[s]);
   }
-  L.n_fe += 6;
-  L.n_att += 1;
 
   // Weighted RMS norm of the embedded error estimate over the true dimension.
   R acc = R(0);
@@ -246,7 +287,7 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
     R eq = R(0);
 #pragma unroll
     for (int j = 0; j < 7; ++j)
-      if (M::E[j] != 0.0) eq += R(M::E[j]) * L.k[j][q];
+      if (M::E[j] != 0.0) eq += K.E[j] * L.k[j][q];
     eq *= hs;
     const R sc = L.atol + L.rtol * rmax(rabs(L.y[q]), rabs(Y[q]));
     const R r = ctl_div(eq, sc);
@@ -259,8 +300,8 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
   constexpr bool kSq = std::is_same<R, float>::value;
   const R err = kSq ? err2 : ctl_sqrt(err2);
   const bool accept = a.ctrl.fixed || err < R(1);
-  if (REC && L.n_att <= a.rec_cap) {
-    const long o = (long)L.inst * a.rec_cap + L.n_att - 1;
+  if (REC && n_att <= a.rec_cap) {
+    const long o = (long)L.inst * a.rec_cap + n_att - 1;
     a.h_rec[o] = accept ? double(hs) : -double(hs);
     a.e_rec[o] = kSq ? sqrt(double(err)) : double(err);  // FP32: err holds err^2
   }
@@ -275,16 +316,26 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
   R fac, lg = R(0);
   if constexpr (kSq) {  // one exp2 for the whole factor
     lg = __builtin_amdgcn_logf(err2);  // log2
-    const R ex = accept ? R(-0.5 * c.beta1) * lg + R(0.5 * c.beta2) * L.err_prev +
-                              R(0.5 * c.beta3) * L.err_prev2
-                        : R(-0.1) * lg;
+    const R ea = fma(R(0.5 * c.beta3), L.err_prev2,
+                     fma(R(0.5 * c.beta2), L.err_prev, R(-0.5 * c.beta1) * lg));
+    const R ex = accept ? ea : R(-0.1) * lg;
     fac = R(c.safety) * __builtin_amdgcn_exp2f(ex);
   } else {
-    fac = R(c.safety) * ctl_pow(err, accept ? R(-c.beta1) : R(-0.2));
-    if (accept) {
-      if (c.beta2 != 0.0) fac = fac * ctl_pow(L.err_prev, R(c.beta2));
-      if (c.beta3 != 0.0) fac = fac * ctl_pow(L.err_prev2, R(c.beta3));
+    constexpr bool kPair = kLanes<R, F> == 2;
+    const R e1 = accept ? R(-c.beta1) : R(-0.2);
+    const bool odd = kPair && (threadIdx.x & 1);
+    const R p = ctl_pow(odd ? L.err_prev : err, odd ? R(c.beta2) : e1);
+    R p2 = R(1);
+    if constexpr (kPair) {
+      const R o = swap_pair(p);
+      fac = R(c.safety) * (odd ? o : p);
+      p2 = odd ? p : o;
+    } else {
+      fac = R(c.safety) * p;
+      if (accept && c.beta2 != 0.0) p2 = ctl_pow(L.err_prev, R(c.beta2));
     }
+    if (c.beta2 != 0.0) fac = accept ? fac * p2 : fac;
+    if (c.beta3 != 0.0 && accept) fac = fac * ctl_pow(L.err_prev2, R(c.beta3));
   }
   fac = (accept && err == R(0)) ? R(c.fac_max) : fac;
   fac = rmax(R(c.fac_min), accept ? rmin(R(c.fac_max), fac) : fac);
@@ -292,11 +343,10 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
   fac = __builtin_isfinite(err) ? fac : R(c.fac_min);
   fac = c.fixed ? R(1) : fac;  // fixed step: h stays
 
-  if (accept) {
-    const double tnew = last ? L.te : L.t + double(hs);
+  if (accept && __builtin_expect(L.tw[0] <= tnew, 0)) {
     // Dense output at this instance's own evaluation times in (t, t_new]
     // (Horner in theta, then the stage combination).
-    while (__builtin_expect(L.tw[0] <= tnew, 0)) {
+    do {
       // theta = (t_e - t_n) / h: the difference in double, the quotient in
       // the state's precision
       const R th = ctl_div(R(L.tw[0] - L.t), hs);
@@ -323,53 +373,59 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
       L.tw[TW - 1] = L.cursor + TW - 1 < a.E
                          ? a.t_eval[(long)L.inst * a.E + L.cursor + TW - 1]
                          : INFINITY;
-    }
-    if (KEEP) {
-      const int i = L.inst;
-      a.dk.t_prev[i] = L.t;
-      a.dk.h_last[i] = hs;
-      write_row<R, N>(a.dk.y_prev + (long)i * a.D, a.D, L.y, L.dim);
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        R qm[N];
-#pragma unroll
-        for (int q = 0; q < N; ++q) {
-          R s2 = R(0);
-#pragma unroll
-          for (int j = 0; j < 7; ++j)
-            if (M::P[j][m] != 0.0) s2 += R(M::P[j][m]) * L.k[j][q];
-          qm[q] = hs * s2;
-        }
-        write_row<R, N>(a.dk.q + ((long)m * a.B + i) * a.D, a.D, qm, L.dim);
-      }
-    }
-    L.t = tnew;
-    if (last) L.status = kSuccess;
-    L.err_prev2 = L.err_prev;
-    if constexpr (kSq)  // log2 max(err, 1e-4)^2 = max(lg, log2 1e-8)
-      L.err_prev = rmax(lg, R(-26.575424759098897));
-    else
-      L.err_prev = rmax(err, R(1e-4));
-    L.n_acc += 1;
+    } while (L.tw[0] <= tnew);
   }
-  L.n_rej += accept ? 0 : 1;
-  L.prev_rej = accept ? 0 : 1;
-  if (accept) {
+  if (KEEP && accept) {
+    const int i = L.inst;
+    a.dk.t_prev[i] = L.t;
+    a.dk.h_last[i] = hs;
+    write_row<R, N>(a.dk.y_prev + (long)i * a.D, a.D, L.y, L.dim);
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      L.y[q] = Y[q];
-      if (kCompensated<R>) L.yc[q] = Yc[q];
-      L.k[0][q] = L.k[6][q];  // FSAL
+    for (int m = 0; m < 4; ++m) {
+      R qm[N];
+#pragma unroll
+      for (int q = 0; q < N; ++q) {
+        R s2 = R(0);
+#pragma unroll
+        for (int j = 0; j < 7; ++j)
+          if (M::P[j][m] != 0.0) s2 += R(M::P[j][m]) * L.k[j][q];
+        qm[q] = hs * s2;
+      }
+      write_row<R, N>(a.dk.q + ((long)m * a.B + i) * a.D, a.D, qm, L.dim);
     }
+  }
+  // commit
+  L.t = accept ? tnew : L.t;
+  R ep;
+  if constexpr (kSq)  // log2 max(err, 1e-4)^2 = max(lg, log2 1e-8)
+    ep = rmax(lg, R(-26.575424759098897));
+  else
+    ep = rmax(err, R(1e-4));
+  // (selects of values: of two members of L they would be of addresses)
+  const R ep1 = L.err_prev, ep2 = L.err_prev2;
+  L.err_prev2 = accept ? ep1 : ep2;
+  L.err_prev = accept ? ep : ep1;
+  L.n_acc += accept ? 1 : 0;
+  L.prev_rej = accept ? 0 : 1;
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    L.y[q] = accept ? Y[q] : L.y[q];
+    if (kCompensated<R>) L.yc[q] = accept ? Yc[q] : L.yc[q];
+    const R k0 = L.k[0][q], k6 = L.k[6][q];
+    L.k[0][q] = accept ? k6 : k0;  // FSAL
   }
   L.h = hs * fac;
-  if (L.status == kRunning && !(double(L.h) > 16.0 * DBL_EPSILON * fabs(L.t)))
-    L.status = kDtUnderflow;
+  const bool under = !(double(L.h) > 16.0 * DBL_EPSILON * fabs(L.t));
+  L.status = accept && last ? kSuccess : under ? kDtUnderflow : kRunning;
 }
 
-template <typename R>
+// LANES: lanes of an instance; the first takes it for all.
+template <int LANES, typename R>
 __device__ __forceinline__ int fetch(const AnalyticArgs<R>& a, int kind) {
-  const int p = atomicAdd(&a.counts[2 + kind], 1);
+  int p = 0;
+  if (LANES == 1 || (threadIdx.x & 1) == 0)
+    p = atomicAdd(&a.counts[2 + kind], 1);
+  if (LANES == 2) p = __builtin_amdgcn_mov_dpp(p, 0xA0, 0xF, 0xF, true);
   const int n = __atomic_load_n(&a.counts[kind], __ATOMIC_RELAXED);
   if (p >= n) return -1;
   return kind == kKindVdp ? a.list[p] : a.list[a.B - 1 - p];
@@ -379,10 +435,12 @@ constexpr int kLongRun = 256;
 
 template <typename R, class M, class F, bool REC, bool KEEP, int TW = 2>
 __global__ __launch_bounds__(256) void solve_kernel(AnalyticArgs<R> a,
-                                                    int kind) {
+                                                    int kind, int per_wave) {
+  if ((threadIdx.x & 63) >= per_wave * kLanes<R, F>) return;
   Lane<R, F::N, TW> L;
   F f;
-  int inst = fetch(a, kind);
+  const Consts<R, M, F::N == 2> K;
+  int inst = fetch<kLanes<R, F>>(a, kind);
   while (inst >= 0) {
     if (a.st.status[inst] == kRunning) {
       load_lane(a, inst, L);
@@ -391,21 +449,34 @@ __global__ __launch_bounds__(256) void solve_kernel(AnalyticArgs<R> a,
       // otherwise the step loop cannot tell them from the evaluation-time
       // prefetch still in flight and waits for everything on every step.
       __builtin_amdgcn_s_waitcnt(0x0F70);
+      // attempts left: of this call, and until the step limit
+      const int lim = max(min(a.budget, a.ctrl.max_steps - L.n_att), 0);
       int used = 0;
-      while (L.status == kRunning && used < a.budget) {
-        attempt<R, M, F, REC, KEEP, TW>(a, L, f);
-        ++used;
+#pragma unroll 1
+      for (int phase = 0; phase < 2; ++phase) {
+        const int end = phase == 0 ? min(lim, kLongRun) : lim;
+        while (L.status == kRunning && used < end) {
+          ++used;
+          attempt<R, M, F, REC, KEEP, TW>(a, L, f, K, L.n_att + used);
+        }
         // An instance still stepping after many attempts is on the batch's
         // critical path (the solve ends with its last step): its wavefront
         // issues ahead of the short-lived ones sharing the SIMD.
-        if (used == kLongRun) __builtin_amdgcn_s_setprio(3);
+        if (phase == 0 && L.status == kRunning && used < lim)
+          __builtin_amdgcn_s_setprio(3);
       }
+      L.n_att += used;
+      L.n_fe += 6 * used;
+      L.n_rej = L.n_att - L.n_acc;
+      if (L.status == kRunning && used < a.budget &&
+          L.n_att >= a.ctrl.max_steps)
+        L.status = kMaxSteps;
       if (L.status == kRunning)
         store_lane(a, L);
       else
         finish_lane(a, L);
     }
-    inst = fetch(a, kind);
+    inst = fetch<kLanes<R, F>>(a, kind);
   }
 }
 
@@ -995,26 +1066,40 @@ hipError_t launch_analytic_init(const AnalyticArgs<R>& a, int, hipStream_t s) {
 
 constexpr int kWindowMinE = 64;
 
+// Instances a wavefront takes.  All its lanes wait while one of them writes
+// an evaluation time, so batches of up to a wavefront per compute unit, and
+// FP32 batches that write one at most steps, are spread over that many (more
+// wavefronts on a unit slow each other, at 512 by a third): 256 FP32
+// instances with 200 times 183 us in four wavefronts, 134 in 256; 4096 with
+// 256 times 303 in 64, 284 in 256, but 64 times 132 and 133; FP64, 4096 with
+// 256 times, 331 and 365.
+constexpr int kSpread = 256, kSpreadE = 128;
+inline int lanes_per_wave(int lanes, int E, bool f32) {
+  if (lanes > kSpread && !(f32 && E >= kSpreadE)) return 64;
+  return std::min(64, std::max(1, (lanes + kSpread - 1) / kSpread));
+}
+
 template <typename R, class M, class F>
-void launch_solve_flags(const AnalyticArgs<R>& a, int kind, dim3 g, dim3 b,
-                        hipStream_t s) {
+void launch_solve_flags(const AnalyticArgs<R>& a, int kind, int per_wave,
+                        dim3 g, dim3 b, hipStream_t s) {
   const bool rec = a.h_rec != nullptr, keep = a.keep_dense != 0;
   // many evaluation times per instance: the eight-time window (measured on
   // the paper's 256-instance, 200-time Van der Pol workload)
   if (!rec && !keep && a.E >= kWindowMinE)
     hipLaunchKernelGGL((solve_kernel<R, M, F, false, false, 8>), g, b, 0, s,
-                       a, kind);
+                       a, kind, per_wave);
   else if (rec && keep)
-    hipLaunchKernelGGL((solve_kernel<R, M, F, true, true>), g, b, 0, s, a, kind);
+    hipLaunchKernelGGL((solve_kernel<R, M, F, true, true>), g, b, 0, s,
+                       a, kind, per_wave);
   else if (rec)
     hipLaunchKernelGGL((solve_kernel<R, M, F, true, false>), g, b, 0, s, a,
-                       kind);
+                       kind, per_wave);
   else if (keep)
     hipLaunchKernelGGL((solve_kernel<R, M, F, false, true>), g, b, 0, s, a,
-                       kind);
+                       kind, per_wave);
   else
     hipLaunchKernelGGL((solve_kernel<R, M, F, false, false>), g, b, 0, s, a,
-                       kind);
+                       kind, per_wave);
 }
 
 template <typename R>
@@ -1023,19 +1108,23 @@ hipError_t launch_analytic_solve(const AnalyticArgs<R>& a, int method,
                                  hipStream_t s) {
   if (block <= 0) block = 64;
   if (lanes <= 0) lanes = a.B;
-  const int grid = (lanes + block - 1) / block;
+  const int width = kind == kKindVdp ? kLanes<R, VdpField<R>> : 1;
+  const int per_wave = std::min(
+      64 / width, lanes_per_wave(lanes, a.E, std::is_same<R, float>::value));
+  const long waves = (lanes + per_wave - 1) / per_wave;
+  const int grid = (int)((waves * 64 + block - 1) / block);
   if (grid == 0) return hipSuccess;
   const dim3 g(grid), b(block);
   if (kind == kKindVdp) {
     if (method == 1)
-      launch_solve_flags<R, Tsit5, VdpField<R>>(a, kind, g, b, s);
+      launch_solve_flags<R, Tsit5, VdpField<R>>(a, kind, per_wave, g, b, s);
     else
-      launch_solve_flags<R, Dopri5, VdpField<R>>(a, kind, g, b, s);
+      launch_solve_flags<R, Dopri5, VdpField<R>>(a, kind, per_wave, g, b, s);
   } else {
     if (method == 1)
-      launch_solve_flags<R, Tsit5, LinearField<R>>(a, kind, g, b, s);
+      launch_solve_flags<R, Tsit5, LinearField<R>>(a, kind, per_wave, g, b, s);
     else
-      launch_solve_flags<R, Dopri5, LinearField<R>>(a, kind, g, b, s);
+      launch_solve_flags<R, Dopri5, LinearField<R>>(a, kind, per_wave, g, b, s);
   }
   return hipGetLastError();
 }
