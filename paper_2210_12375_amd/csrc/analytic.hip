@@ -99,10 +99,12 @@ __device__ __forceinline__ double swap_pair(double x) {
 template <typename R, class M, bool HOLD>
 struct Consts {
   R A[7][7], E[7];
+  R lo, hi;  // bounds of a step's factor (fixed step: 1)
   __device__ __forceinline__ static void hold(R& x) {
     if constexpr (HOLD) asm volatile("" : "+v"(x));
   }
-  __device__ __forceinline__ Consts() {
+  __device__ __forceinline__ explicit Consts(const Ctrl& c)
+      : lo(R(c.fixed ? 1.0 : c.fac_min)), hi(R(c.fixed ? 1.0 : c.fac_max)) {
 #pragma unroll
     for (int s = 0; s < 7; ++s) {
 #pragma unroll
@@ -141,6 +143,8 @@ struct Lane {
   double tw[TW];
   R h, err_prev, err_prev2, rtol, atol;
   int32_t n_att, n_acc, n_rej, n_fe, status, cursor, prev_rej, dim, inst;
+  R cap;  // most a step may grow by after an acceptance: 1 after a rejection
+  uint32_t odd, in[N];  // lane masks: second of a pair; component q < dim
 };
 
 template <typename R, int N>
@@ -240,17 +244,17 @@ __device__ __forceinline__ void finish_lane(const AnalyticArgs<R>& a,
 // REC: write the attempt record; KEEP: keep the interpolant for solver_eval.
 // Controller and commit are branch-free (selects), a taken branch costs a lone
 // wavefront several instructions; only the dense output branches.  n_att: this
-// attempt's number.
+// attempt's number.  Returns whether it was the instance's last (t_end or the
+// smallest step reached).
 template <typename R, class M, class F, bool REC, bool KEEP, int TW>
-__device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
+__device__ __forceinline__ bool attempt(const AnalyticArgs<R>& a,
                                         Lane<R, F::N, TW>& L, const F& f,
                                         const Consts<R, M, F::N == 2>& K,
                                         [[maybe_unused]] int n_att) {
   constexpr int N = F::N;
-  const double tsum = L.t + double(L.h);
-  const bool last = tsum >= L.te;
-  const double tnew = last ? L.te : tsum;
-  const R hs = last ? R(L.te - L.t) : L.h;
+  const double tsum = L.t + double(L.h), tnew = fmin(tsum, L.te);
+  const uint32_t mlast = lane_mask(tsum >= L.te);
+  const R hs = pick(mlast, R(L.te - L.t), L.h);
 
   // Stages 2..7: Y_s = y + h sum_{j<s} a_sj k_j, k_s = f(t + c_s h, Y_s).
   // (The fields here are autonomous, so the stage time is not formed.)
@@ -281,7 +285,7 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
   }
 
   // Weighted RMS norm of the embedded error estimate over the true dimension.
-  R acc = R(0);
+  R r[N];
 #pragma unroll
   for (int q = 0; q < N; ++q) {
     R eq = R(0);
@@ -289,9 +293,20 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
     for (int j = 0; j < 7; ++j)
       if (M::E[j] != 0.0) eq += K.E[j] * L.k[j][q];
     eq *= hs;
-    const R sc = L.atol + L.rtol * rmax(rabs(L.y[q]), rabs(Y[q]));
-    const R r = ctl_div(eq, sc);
-    if (N == 2 || q < L.dim) acc += r * r;
+    const R sc = L.atol + L.rtol * fmax(fabs(L.y[q]), fabs(Y[q]));
+    r[q] = ctl_div(eq, sc);
+  }
+  // (components past an instance's dimension, zero over their scale, count
+  // as zeros also where the scale is zero)
+  R acc = R(0);
+  if constexpr (N == 2) {
+    acc = fma(r[0], r[0], r[1] * r[1]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const R v = keep(L.in[q], r[q]);
+      acc = fma(v, v, acc);
+    }
   }
   // err^2 (mean of the squares); FP64 takes the root as written, FP32 works
   // with the square: err < 1 iff err^2 < 1, and both powers of the
@@ -300,6 +315,7 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
   constexpr bool kSq = std::is_same<R, float>::value;
   const R err = kSq ? err2 : ctl_sqrt(err2);
   const bool accept = a.ctrl.fixed || err < R(1);
+  const uint32_t macc = lane_mask(accept);
   if (REC && n_att <= a.rec_cap) {
     const long o = (long)L.inst * a.rec_cap + n_att - 1;
     a.h_rec[o] = accept ? double(hs) : -double(hs);
@@ -318,30 +334,31 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
     lg = __builtin_amdgcn_logf(err2);  // log2
     const R ea = fma(R(0.5 * c.beta3), L.err_prev2,
                      fma(R(0.5 * c.beta2), L.err_prev, R(-0.5 * c.beta1) * lg));
-    const R ex = accept ? ea : R(-0.1) * lg;
+    const R ex = pick(macc, ea, R(-0.1) * lg);
     fac = R(c.safety) * __builtin_amdgcn_exp2f(ex);
   } else {
     constexpr bool kPair = kLanes<R, F> == 2;
-    const R e1 = accept ? R(-c.beta1) : R(-0.2);
-    const bool odd = kPair && (threadIdx.x & 1);
-    const R p = ctl_pow(odd ? L.err_prev : err, odd ? R(c.beta2) : e1);
+    const R e1 = pick(macc, R(-c.beta1), R(-0.2));
     R p2 = R(1);
     if constexpr (kPair) {
+      const R p = ctl_pow(pick(L.odd, L.err_prev, err),
+                          pick(L.odd, R(c.beta2), e1));
       const R o = swap_pair(p);
-      fac = R(c.safety) * (odd ? o : p);
-      p2 = odd ? p : o;
+      fac = R(c.safety) * pick(L.odd, o, p);
+      p2 = pick(L.odd, p, o);
     } else {
-      fac = R(c.safety) * p;
+      fac = R(c.safety) * ctl_pow(err, e1);
       if (accept && c.beta2 != 0.0) p2 = ctl_pow(L.err_prev, R(c.beta2));
     }
-    if (c.beta2 != 0.0) fac = accept ? fac * p2 : fac;
+    if (c.beta2 != 0.0) fac = pick(macc, fac * p2, fac);
     if (c.beta3 != 0.0 && accept) fac = fac * ctl_pow(L.err_prev2, R(c.beta3));
   }
-  fac = (accept && err == R(0)) ? R(c.fac_max) : fac;
-  fac = rmax(R(c.fac_min), accept ? rmin(R(c.fac_max), fac) : fac);
-  fac = (accept && L.prev_rej) ? rmin(R(1), fac) : fac;
-  fac = __builtin_isfinite(err) ? fac : R(c.fac_min);
-  fac = c.fixed ? R(1) : fac;  // fixed step: h stays
+  // (err = 0 gives an infinite factor by itself, but for beta1 = 0; of a NaN
+  // the maximum is fac_min)
+  if (c.beta1 == 0.0) fac = (accept && err == R(0)) ? R(c.fac_max) : fac;
+  fac = fmax(K.lo, fac);
+  fac = fmin(pick(macc, K.hi, R(INFINITY)), fac);
+  fac = fmin(pick(macc, L.cap, R(INFINITY)), fac);
 
   if (accept && __builtin_expect(L.tw[0] <= tnew, 0)) {
     // Dense output at this instance's own evaluation times in (t, t_new]
@@ -395,28 +412,25 @@ __device__ __forceinline__ void attempt(const AnalyticArgs<R>& a,
     }
   }
   // commit
-  L.t = accept ? tnew : L.t;
+  L.t = pick(macc, tnew, L.t);
   R ep;
   if constexpr (kSq)  // log2 max(err, 1e-4)^2 = max(lg, log2 1e-8)
-    ep = rmax(lg, R(-26.575424759098897));
+    ep = fmax(lg, R(-26.575424759098897));
   else
-    ep = rmax(err, R(1e-4));
-  // (selects of values: of two members of L they would be of addresses)
-  const R ep1 = L.err_prev, ep2 = L.err_prev2;
-  L.err_prev2 = accept ? ep1 : ep2;
-  L.err_prev = accept ? ep : ep1;
-  L.n_acc += accept ? 1 : 0;
-  L.prev_rej = accept ? 0 : 1;
+    ep = fmax(err, R(1e-4));
+  L.err_prev2 = pick(macc, L.err_prev, L.err_prev2);
+  L.err_prev = pick(macc, ep, L.err_prev);
+  L.n_acc -= (int32_t)macc;
+  L.cap = pick(macc, R(INFINITY), R(1));
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    L.y[q] = accept ? Y[q] : L.y[q];
-    if (kCompensated<R>) L.yc[q] = accept ? Yc[q] : L.yc[q];
-    const R k0 = L.k[0][q], k6 = L.k[6][q];
-    L.k[0][q] = accept ? k6 : k0;  // FSAL
+    L.y[q] = pick(macc, Y[q], L.y[q]);
+    if (kCompensated<R>) L.yc[q] = pick(macc, Yc[q], L.yc[q]);
+    L.k[0][q] = pick(macc, L.k[6][q], L.k[0][q]);  // FSAL
   }
   L.h = hs * fac;
   const bool under = !(double(L.h) > 16.0 * DBL_EPSILON * fabs(L.t));
-  L.status = accept && last ? kSuccess : under ? kDtUnderflow : kRunning;
+  return (accept && tsum >= L.te) || under;
 }
 
 // LANES: lanes of an instance; the first takes it for all.
@@ -439,12 +453,16 @@ __global__ __launch_bounds__(256) void solve_kernel(AnalyticArgs<R> a,
   if ((threadIdx.x & 63) >= per_wave * kLanes<R, F>) return;
   Lane<R, F::N, TW> L;
   F f;
-  const Consts<R, M, F::N == 2> K;
+  const Consts<R, M, F::N == 2> K(a.ctrl);
   int inst = fetch<kLanes<R, F>>(a, kind);
   while (inst >= 0) {
     if (a.st.status[inst] == kRunning) {
       load_lane(a, inst, L);
       f.load(a, inst, L.dim);
+      L.cap = L.prev_rej ? R(1) : R(INFINITY);
+      L.odd = lane_mask(kLanes<R, F> == 2 && (threadIdx.x & 1));
+#pragma unroll
+      for (int q = 0; q < F::N; ++q) L.in[q] = lane_mask(q < L.dim);
       // Drain the lane's loads here (vmcnt 0; expcnt, lgkmcnt untouched):
       // otherwise the step loop cannot tell them from the evaluation-time
       // prefetch still in flight and waits for everything on every step.
@@ -452,19 +470,21 @@ __global__ __launch_bounds__(256) void solve_kernel(AnalyticArgs<R> a,
       // attempts left: of this call, and until the step limit
       const int lim = max(min(a.budget, a.ctrl.max_steps - L.n_att), 0);
       int used = 0;
+      bool done = false;
 #pragma unroll 1
       for (int phase = 0; phase < 2; ++phase) {
         const int end = phase == 0 ? min(lim, kLongRun) : lim;
-        while (L.status == kRunning && used < end) {
+        while (!done && used < end) {
           ++used;
-          attempt<R, M, F, REC, KEEP, TW>(a, L, f, K, L.n_att + used);
+          done = attempt<R, M, F, REC, KEEP, TW>(a, L, f, K, L.n_att + used);
         }
         // An instance still stepping after many attempts is on the batch's
         // critical path (the solve ends with its last step): its wavefront
         // issues ahead of the short-lived ones sharing the SIMD.
-        if (phase == 0 && L.status == kRunning && used < lim)
-          __builtin_amdgcn_s_setprio(3);
+        if (phase == 0 && !done && used < lim) __builtin_amdgcn_s_setprio(3);
       }
+      L.prev_rej = L.cap == R(1);
+      if (done) L.status = L.t >= L.te ? kSuccess : kDtUnderflow;
       L.n_att += used;
       L.n_fe += 6 * used;
       L.n_rej = L.n_att - L.n_acc;
