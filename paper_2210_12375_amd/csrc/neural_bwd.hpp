@@ -25,10 +25,15 @@ struct BwdArgs {
   float* lam;
   VjpDenseT<float> dense;
   // Continuous adjoint (mu != null): stage s1 only, mu [B, D] = J^T kap of
-  // the rows with status kRunning, at times t + c h.
+  // the rows with status kRunning, at times t + c h, with the stage's adjoint
+  // kap [B, D] = a0 - h sum_j coef[j] muj[j] formed here and stored.
   float* mu;
   int s1;
-  const float* kap;
+  float* kap;
+  const float* a0;
+  const float* muj[6];
+  float coef[6];
+  int nc;
   const int32_t* status;
   const float* hs;
   const double* t;
