@@ -28,8 +28,8 @@ struct F64Args {
   int kslot;
 };
 
-// One stage of the adjoint (MfmaVjpArgs' meaning); the forward layers are
-// always read from act_in.
+// One stage of the adjoint (BwdArgs' meaning, stage by stage); the forward
+// layers are always read from act_in.
 struct F64VjpArgs {
   int B, D, din, H, cnf;
   const int32_t* act;

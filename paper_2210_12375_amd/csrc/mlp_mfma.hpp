@@ -79,37 +79,4 @@ MfmaArgs mfma_args(int B, int D, int din, int H, int cnf, const int32_t* status,
                    const float* y, const float* K, float* Y7, const float* hs,
                    const double* t, const float* eps, const MfmaWeights& w);
 
-// One stage s of the discrete adjoint for a batch of rows: mu_s =
-// J_f(Y_s)^T kappa_s on MFMA (the field's hidden layers recomputed), the
-// stage's entries of the parameter-gradient tape, and the row updates
-// kappa_j += h a_sj mu_s, lambda_next += mu_s (Lambda = lambda + mu at the
-// last stage, lambda = lambda_next after the first).
-struct MfmaVjpArgs {
-  int B, D, din, H, cnf;
-  const int32_t* act;  // rows with kRunning are differentiated
-  const float* Y;      // [B, D] stage input
-  const float* kap_s;  // [B, D] kappa_s
-  const float* eps;    // [B, D] probe (CNF)
-  const float* bh;     // [B] step size
-  const double* bt;    // [B] t_n
-  double c;            // c_s
-  MfmaWeights w;
-  // tape, sample-major [K][feature]; this stage's rows start at kb
-  float *T1in, *T1g, *T2in, *T2g, *T3in, *T3g;
-  long K, kb;
-  int s, n;
-  int kidx[6];
-  float coef[6];
-  float *lam, *lamn, *kap;  // kap: [7, B, D]
-  // Continuous adjoint: if not null, mu_s is stored here ([B, D], zero in
-  // the columns the field does not read) instead of the row updates above.
-  float* mu_out;
-  // If not null, the hidden layers' values of this stage as a field kernel
-  // stored them (MfmaArgs::act_out's layout): the two forward layers are
-  // read instead of recomputed.
-  const float* act_in;
-};
-
-hipError_t launch_vjp_mfma(const MfmaVjpArgs& a, hipStream_t s);
-
 }  // namespace bode

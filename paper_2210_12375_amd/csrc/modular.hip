@@ -1717,47 +1717,7 @@ hipError_t launch_vjp(const Mod<R>& m, const Back<R>& b, const VjpSpec& sp,
   return hipGetLastError();
 }
 
-// The matrix-core VJP kernel's arguments for stage sp.s of the step.
-MfmaVjpArgs vjp_args(const ModImpl& im, const Mod<float>& m,
-                     const Back<float>& b, const VjpSpec& sp) {
-  MfmaVjpArgs a{};
-  a.B = m.B;
-  a.D = m.D;
-  a.din = m.d_in;
-  a.H = m.H;
-  a.cnf = m.cnf;
-  a.act = b.act;
-  a.Y = sp.Y != nullptr ? static_cast<const float*>(sp.Y)
-                        : b.Ys + (long)(sp.s - 1) * m.B * m.D;
-  a.act_in = static_cast<const float*>(sp.act_in);
-  a.kap_s = b.kap + (long)(sp.s - 1) * m.B * m.D;
-  a.eps = m.eps;
-  a.bh = b.bh;
-  a.bt = b.bt;
-  a.c = sp.c;
-  a.w = im.mw;
-  a.T1in = b.T1in;
-  a.T1g = b.T1g;
-  a.T2in = b.T2in;
-  a.T2g = b.T2g;
-  a.T3in = b.T3in;
-  a.T3g = b.T3g;
-  a.K = b.K;
-  a.kb = sp.kbase + (long)(sp.s - 1) * (m.cnf ? 2L * m.B : (long)m.B);
-  a.s = sp.s;
-  a.n = sp.n;
-  for (int j = 0; j < sp.n; ++j) {
-    a.kidx[j] = sp.kidx[j];
-    a.coef[j] = float(sp.coef[j]);
-  }
-  a.lam = b.lam;
-  a.lamn = b.lamn;
-  a.kap = b.kap;
-  a.mu_out = static_cast<float*>(sp.mu_out);
-  return a;
-}
-
-// BF16 mode: the adjoint stages of one step (or, mu set, one stage) from
+// The adjoint stages of one step (or, mu set, one stage) from
 // the stored stage inputs Yh and layers Ah of its seven stages.
 BwdArgs bwd_args(const Mod<float>& m, const Back<float>& b, const float* Yh,
                  const float* Ah, long kbase) {
@@ -1834,21 +1794,18 @@ F64VjpArgs vjp_args64(const Mod<double>& m, const Back<double>& b,
   return a;
 }
 
-// Matrix-core modes: the stage's VJP on MFMA (BF16: BF16 weights, three-way
-// split activations and cotangents; FP32: FP32 operands; both accumulate in
-// FP32); else the FMA kernel.
+// One stage's VJP: FP64 on the matrix cores where the layers are stored, else
+// the FMA kernel.
 template <typename R>
-hipError_t vjp(const ModImpl& im, const Mod<R>& m, const Back<R>& b,
-               const VjpSpec& sp, hipStream_t s) {
-  if constexpr (std::is_same<R, float>::value) {
-    if (im.mw.packedT != nullptr)
-      return launch_vjp_mfma(vjp_args(im, m, b, sp), s);
-  } else if (m.wpT != nullptr && sp.act_in != nullptr) {
-    F64VjpSteps v{};
-    v.n = 1;
-    v.st[0] = vjp_args64(m, b, sp);
-    return launch_vjp_f64(v, s);
-  }
+hipError_t vjp(const Mod<R>& m, const Back<R>& b, const VjpSpec& sp,
+               hipStream_t s) {
+  if constexpr (!std::is_same<R, float>::value)
+    if (m.wpT != nullptr && sp.act_in != nullptr) {
+      F64VjpSteps v{};
+      v.n = 1;
+      v.st[0] = vjp_args64(m, b, sp);
+      return launch_vjp_f64(v, s);
+    }
   return launch_vjp<R>(m, b, sp, s);
 }
 
@@ -2594,12 +2551,6 @@ namespace {
 
 inline dim3 lin_grid(long n) { return dim3((unsigned)((n + 255) / 256)); }
 
-// At most two 16-row tiles (CNF: 8 instances) per compute unit.
-template <typename R>
-bool few_tiles(const Mod<R>& m) {
-  return (m.B + (m.cnf ? 7 : 15)) / (m.cnf ? 8 : 16) <= 512;
-}
-
 template <typename R, class M>
 hipError_t stages(ModImpl& im, Mod<R> v, Back<R>& b, R* y7dst, bool keep_y,
                   hipStream_t s) {
@@ -2745,13 +2696,12 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
       if (r != hipSuccess) return r;
     }
     // the seven stages and the dense-output part in one launch on the
-    // matrix cores; BF16 batches of many tiles take one launch each (a CNF
-    // step of 8192 instances: the one launch is no faster alone, and holds
-    // the compute units the parameter-gradient products would share)
+    // matrix cores (against a launch a stage: 20,000 CNF instances of width
+    // 64 6.29 -> 5.61 ms a training step, 9000 MLP instances of width 256
+    // 4.59 -> 4.40, the CNF of 8192 at width 512 the same)
     F64VjpSteps vs{};
-    const bool eng = std::is_same<R, float>::value && mat &&
-                     (im.mw.f32 || few_tiles(m));
-    const bool steps = eng || (mat && !std::is_same<R, float>::value);
+    const bool eng = std::is_same<R, float>::value && mat;
+    const bool steps = mat;
     VjpDenseT<R> dense{};
     if (steps) {
       {
@@ -2821,7 +2771,7 @@ hipError_t backward_t(ModImpl& im, Mod<R>& m, Back<R>& b, const R* g_eval,
           vs.st[vs.n++] = vjp_args64(m, b, sp);
         continue;
       }
-      const hipError_t r = vjp<R>(im, m, b, sp, s);
+      const hipError_t r = vjp<R>(m, b, sp, s);
       if (r != hipSuccess) return r;
     }
     if constexpr (!std::is_same<R, float>::value) {

@@ -207,7 +207,6 @@ __host__ __device__ inline Lds lds_map(int din) {
   return l;
 }
 
-typedef mtile::Bf3 PackOp;
 
 // One k block's weight fragments of NT feature tiles.
 template <class S, int NT>
