@@ -263,10 +263,11 @@ __device__ __forceinline__ void field_tile(const F64Args& a, int r0,
             kl[(a.kslot * PR + r) * D + n] = acc[g][0];
           else if (row < B)
             a.out[(long)row * D + n] = acc[g][0];
-          // probe times tangent output (A0 is free: every wave is past
-          // layer 2)
+          // probe times tangent output, into the inputs' rows (free: every
+          // wave is past layer 1; the layer buffers' rows are as wide as
+          // the hidden layer, which may be narrower than the state)
           if (CNF)
-            A0[r * d.SA + n] =
+            X[r * d.SX + n] =
                 row < B ? a.eps[(long)row * D + n] * acc[MP + g][0] : 0.0;
         }
       }
@@ -277,7 +278,7 @@ __device__ __forceinline__ void field_tile(const F64Args& a, int r0,
       for (int r = tid; r < PR; r += blockDim.x) {
         const int row = r0 + r;
         double q = 0.0;
-        for (int j = 0; j < din; ++j) q += A0[r * d.SA + j];
+        for (int j = 0; j < din; ++j) q += X[r * d.SX + j];
         if (KL)
           kl[(a.kslot * PR + r) * D + din] = -q;
         else if (row < B)
