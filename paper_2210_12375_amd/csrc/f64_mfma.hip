@@ -76,7 +76,7 @@ __global__ __launch_bounds__(64 * kWV) void vjp64_kernel(F64VjpSteps v) {
 
 bool f64_fits(int D, int din, int H, bool cnf) {
   (void)D;
-  return sizeof(double) * lds_elems(cnf ? 8 : 4, din, H) <= kLdsMax;
+  return tile_fits(din, H, cnf);
 }
 
 size_t f64_packed_elems(int din, int H) {
@@ -117,16 +117,14 @@ hipError_t launch_field_f64(const F64Steps& v0, hipStream_t s) {
     constexpr int MT = mt(), NT = nt(), PR = cnf() ? 2 * MT : 4 * MT;
     constexpr bool CNF = cnf();
     F64Steps v = v0;
-    size_t sm = sizeof(double) * lds_elems(4 * MT, a.din, a.H);
-    v.kl_off = (int)sm;
-    const size_t smk = sm + sizeof(double) * 7 * PR * (size_t)a.D;
-    const bool kl = v.kl && smk <= kLdsMax;
-    if (kl) sm = smk;
-    auto k = kl ? field64_kernel<MT, NT, CNF, true>
-                : field64_kernel<MT, NT, CNF, false>;
-    const hipError_t e = allow_lds(k, sm);
+    const LdsPlan p = lds_plan(MT, a.D, a.din, a.H, CNF, v.kl ? 7 : 0);
+    v.kl_off = p.off;
+    auto k = p.block ? field64_kernel<MT, NT, CNF, true>
+                     : field64_kernel<MT, NT, CNF, false>;
+    const hipError_t e = allow_lds(k, p.bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3((a.B + PR - 1) / PR), dim3(64 * kWV), sm, s, v);
+    hipLaunchKernelGGL(k, dim3((a.B + PR - 1) / PR), dim3(64 * kWV), p.bytes,
+                       s, v);
     return hipGetLastError();
   });
 }
@@ -138,17 +136,15 @@ hipError_t launch_vjp_f64(const F64VjpSteps& v0, hipStream_t s) {
     constexpr int MT = mt(), NT = nt(), PR = cnf() ? 2 * MT : 4 * MT;
     constexpr bool CNF = cnf();
     F64VjpSteps v = v0;
-    size_t sm = sizeof(double) * lds_elems(4 * MT, a.din, a.H);
-    v.cl_off = (int)sm;
     // the cotangent block in LDS where this launch also seeds it
-    const size_t smc = sm + sizeof(double) * 8 * PR * (size_t)a.D;
-    const bool cl = v.dense.on && smc <= kLdsMax;
-    if (cl) sm = smc;
-    auto k = cl ? vjp64_kernel<MT, NT, CNF, true>
-                : vjp64_kernel<MT, NT, CNF, false>;
-    const hipError_t e = allow_lds(k, sm);
+    const LdsPlan p = lds_plan(MT, a.D, a.din, a.H, CNF, v.dense.on ? 8 : 0);
+    v.cl_off = p.off;
+    auto k = p.block ? vjp64_kernel<MT, NT, CNF, true>
+                     : vjp64_kernel<MT, NT, CNF, false>;
+    const hipError_t e = allow_lds(k, p.bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3((a.B + PR - 1) / PR), dim3(64 * kWV), sm, s, v);
+    hipLaunchKernelGGL(k, dim3((a.B + PR - 1) / PR), dim3(64 * kWV), p.bytes,
+                       s, v);
     return hipGetLastError();
   });
 }

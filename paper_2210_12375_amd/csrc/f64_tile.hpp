@@ -31,6 +31,7 @@
 
 #include "common.hpp"
 #include "f64_mfma.hpp"
+#include "f64_shape.hpp"
 
 namespace bode {
 namespace f64t {
@@ -78,33 +79,6 @@ __device__ __forceinline__ double tanh64(double x) {
   t = fma(fma(-dl, t, fma(-d, t, -m) - ml), v, t);
   t = y > 40.0 ? 1.0 : t;  // (infinities too)
   return copysign(t, x);
-}
-
-constexpr int kWV = 8;     // wavefronts per tile
-constexpr int kPad = 8;    // LDS row padding (doubles): rows 64 bytes apart
-constexpr int kFrag = 128; // elements per fragment
-
-struct Dims {
-  int nk1, nkd, nkh, nnh, nnd;  // k blocks of 8, column tiles of 16
-  int SX, SA;                   // LDS row strides
-};
-
-__host__ __device__ inline Dims dims(int din, int H) {
-  Dims d;
-  d.nk1 = (din + 1 + 7) / 8;  // inputs and the time feature
-  d.nkd = (din + 7) / 8;
-  d.nkh = (H + 7) / 8;
-  d.nnh = (H + 15) / 16;
-  d.nnd = (din + 15) / 16;
-  d.SX = d.nk1 * 8 + kPad;
-  d.SA = d.nnh * 16 + kPad;
-  return d;
-}
-
-// LDS doubles of a tile of RT rows: inputs and two layer buffers.
-__host__ __device__ inline size_t lds_elems(int RT, int din, int H) {
-  const Dims d = dims(din, H);
-  return (size_t)RT * (d.SX + 2 * d.SA);
 }
 
 // C[MT][NT] += A (LDS, 4 MT rows) x column tiles nb0 .. nb0 + NT - 1 of the
@@ -480,19 +454,6 @@ __device__ __forceinline__ void vjp_tile(const F64VjpArgs& a, int r0,
 }
 
 // ---- tile shapes -------------------------------------------------------------
-
-constexpr size_t kLdsMax = 160 * 1024;
-
-// 4-row groups of a tile (MT, tangent rows included): as many as still give
-// every compute unit a tile, 4 instances up to 1024 of them, 8 to 2048, then
-// 16 (CNF: 4, then 8 with their tangents), while the layers fit in LDS.
-inline int row_groups(int B, int din, int H, bool cnf) {
-  int mt = cnf ? (B > 1024 ? 4 : 2) : (B > 2048 ? 4 : B > 1024 ? 2 : 1);
-  while (mt > (cnf ? 2 : 1) &&
-         sizeof(double) * lds_elems(4 * mt, din, H) > kLdsMax)
-    mt /= 2;
-  return mt;
-}
 
 // Calls f(integral constants MT, NT, CNF) for the shape.
 template <class F>

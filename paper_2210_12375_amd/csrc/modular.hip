@@ -757,17 +757,15 @@ hipError_t fused64_launch(const Mod<double>& m, Fused64Args f,
       m.B, m.d_in, m.H, m.cnf, [&](auto mt, auto nt, auto cnf) {
         constexpr int MT = mt(), NT = nt(), PR = cnf() ? 2 * MT : 4 * MT;
         constexpr bool CNF = cnf();
-        size_t sm = sizeof(double) * f64t::lds_elems(4 * MT, m.d_in, m.H);
-        f.kl_off = (int)sm;
-        const size_t smk = sm + sizeof(double) * 7 * PR * (size_t)m.D;
-        const bool kl = smk <= f64t::kLdsMax;
-        if (kl) sm = smk;
-        auto k = kl ? solve_fused64_kernel<MT, NT, CNF, M, true>
-                    : solve_fused64_kernel<MT, NT, CNF, M, false>;
-        const hipError_t e = f64t::allow_lds(k, sm);
+        const f64t::LdsPlan p =
+            f64t::lds_plan(MT, m.D, m.d_in, m.H, CNF, 7);
+        f.kl_off = p.off;
+        auto k = p.block ? solve_fused64_kernel<MT, NT, CNF, M, true>
+                         : solve_fused64_kernel<MT, NT, CNF, M, false>;
+        const hipError_t e = f64t::allow_lds(k, p.bytes);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k, dim3((m.B + PR - 1) / PR), dim3(64 * f64t::kWV),
-                           sm, s, m, f);
+                           p.bytes, s, m, f);
         return hipGetLastError();
       });
 }
