@@ -1129,6 +1129,7 @@ hipError_t launch_analytic_solve(const AnalyticArgs<R>& a, int method,
   if (block <= 0) block = 64;
   if (lanes <= 0) lanes = a.B;
   const int width = kind == kKindVdp ? kLanes<R, VdpField<R>> : 1;
+  if (width == 2) block += block & 1;  // (both lanes of a pair)
   const int per_wave = std::min(
       64 / width, lanes_per_wave(lanes, a.E, std::is_same<R, float>::value));
   const long waves = (lanes + per_wave - 1) / per_wave;
