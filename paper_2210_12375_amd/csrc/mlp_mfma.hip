@@ -35,8 +35,8 @@ struct PackJobs {
 
 // A thread packs one lane's eight elements of a fragment (one 16-byte store
 // per plane); the last grid row does the vector block.  Terms are rounded to
-// nearest (beyond 2^127 cut, so that none overflows) and each residual is
-// exact; one plane is the BF16 weight itself.
+// nearest (from kBigValue on cut, infinities cut from the largest float) and
+// each residual is exact; one plane is the BF16 weight itself.
 __global__ void pack_weights_kernel(PackJobs p) {
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int nthr = gridDim.x * blockDim.x;
@@ -55,6 +55,13 @@ __global__ void pack_weights_kernel(PackJobs p) {
                    ? j.W[j.trans ? (long)n * j.ldw + k : (long)k * j.ldw + n]
                    : 0.f;
       }
+      uint32_t big = 0;
+      if (p.planes > 1)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          big |= uint32_t(!(fabsf(v[i]) < kBigValue)) << i;
+          if (fabsf(v[i]) > FLT_MAX) v[i] = copysignf(FLT_MAX, v[i]);
+        }
       for (int q = 0; q < p.planes; ++q) {
         uint32_t w[4];
 #pragma unroll
@@ -63,10 +70,9 @@ __global__ void pack_weights_kernel(PackJobs p) {
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
             float& x = v[i + u];
-            const bool big = p.planes > 1 && !(fabsf(x) < 1.7014118e38f);
-            h[u] = big ? uint16_t(__float_as_uint(x) >> 16) : f2bf(x);
-            const float hv = __uint_as_float((uint32_t)h[u] << 16);
-            x = __builtin_isfinite(hv) ? x - hv : 0.f;
+            h[u] = big >> (i + u) & 1 ? uint16_t(__float_as_uint(x) >> 16)
+                                      : f2bf(x);
+            x -= __uint_as_float((uint32_t)h[u] << 16);
           }
           w[i / 2] = h[0] | ((uint32_t)h[1] << 16);
         }

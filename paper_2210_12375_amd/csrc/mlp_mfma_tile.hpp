@@ -72,6 +72,10 @@ __host__ __device__ inline DimsT dims_t(int din, int H) {
   return d;
 }
 
+// FP32 mode cuts (rather than rounds) weights and stage inputs from here on
+// into BF16 terms (put4 of neural_tile.hpp gives the reason).
+constexpr float kBigValue = 512.f;
+
 __device__ __forceinline__ bf16x8 lds8(const uint16_t* p) {
   return *reinterpret_cast<const bf16x8*>(p);
 }

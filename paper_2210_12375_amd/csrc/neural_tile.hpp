@@ -39,6 +39,7 @@ namespace bode {
 namespace ntile {
 
 using mtile::fast_tanh;
+using mtile::kBigValue;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -107,21 +108,44 @@ __device__ __forceinline__ float hi_f(uint32_t u) {
   return __uint_as_float(u & 0xffff0000u);
 }
 
-// Four values as BF16 terms (rounded to nearest; each residual is exact, so
-// three terms sum to the value), one 8-byte store per term.  SAFE: values
-// beyond 2^127 (whose rounding could overflow) keep their top 16 bits.
-template <int kA, bool SAFE>
+// Four values as BF16 terms that sum to them, one 8-byte store per term,
+// rounded to nearest; each residual is exact.
+//
+// kInput (stage inputs, any float): a product that overflows has to come out as
+// the infinity of its sign, as a plain FP32 product would, so that the unit
+// saturates; terms of both signs would give NaN.  In the BF16 mode all values
+// are cut instead of rounded (exact as well, and every term has the value's
+// sign).  FP32 mode, whose cut terms would drop more of a product, cuts values
+// from 512 on, as the packed weights are (a product whose small part overflows
+// has both factors beyond it), and bounds them by 2^119 (every unit with a
+// weight above 2^-115 is saturated there, and what 256 of them drop stays
+// below 2^128); an infinity is then no special case.
+// kCotangent (any float, not to be bounded): cut where rounding could overflow.
+enum PutKind { kPlain, kInput, kCotangent };
+template <class Op, PutKind KIND>
 __device__ __forceinline__ void put4(uint16_t* p, int plane, f32x4 v) {
   // (the residuals are of the rounded value: no fusing with its product)
 #pragma clang fp contract(off)
-  f32x4 h = v;
-  if (SAFE) {
+  constexpr int kA = Op::kA;
+  constexpr bool kCut = KIND != kPlain && !Op::kTwo && kA > 1;
+  constexpr float kBig = KIND == kInput && Op::kTwo ? kBigValue : 0x1p127f;
+  if constexpr (kCut) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (!(fabsf(v[i]) < 1.7014118e38f))
-        h[i] = __uint_as_float(__float_as_uint(v[i]) & 0xffff0000u);
+    for (int k = 0; k < kA; ++k) {
+      uint32_t w[2];
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        w[i / 2] = __builtin_amdgcn_perm(
+            __float_as_uint(v[i + 1]), __float_as_uint(v[i]), 0x07060302u);
+        v[i] -= lo_f(w[i / 2]);
+        v[i + 1] -= hi_f(w[i / 2]);
+      }
+      *reinterpret_cast<u32x2*>(p + k * plane) = u32x2{w[0], w[1]};
+    }
+    return;
   }
-  uint32_t a = pack2(h[0], h[1]), b = pack2(h[2], h[3]);
+  const f32x4 u = v;
+  uint32_t a = pack2(v[0], v[1]), b = pack2(v[2], v[3]);
   *reinterpret_cast<u32x2*>(p) = u32x2{a, b};
 #pragma unroll
   for (int k = 1; k < kA; ++k) {
@@ -132,6 +156,27 @@ __device__ __forceinline__ void put4(uint16_t* p, int plane, f32x4 v) {
     a = pack2(v[0], v[1]);
     b = pack2(v[2], v[3]);
     *reinterpret_cast<u32x2*>(p + k * plane) = u32x2{a, b};
+  }
+  if constexpr (KIND != kPlain) {
+    // (written over afterwards: 2916 us against 2995 to 3050 with the selects
+    // or the two paths ahead of the stores, 40,000 FP32 instances)
+    const bool big = !(fmaxf(fmaxf(fabsf(u[0]), fabsf(u[1])),
+                             fmaxf(fabsf(u[2]), fabsf(u[3]))) < kBig);
+    if (__builtin_expect(__any(big), 0)) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        float x = u[i];
+        if (!(fabsf(x) < kBig)) {
+          if (KIND == kInput && Op::kTwo && fabsf(x) > 0x1p119f)
+            x = copysignf(0x1p119f, x);
+#pragma unroll
+          for (int k = 0; k < kA; ++k) {
+            p[k * plane + i] = uint16_t(__float_as_uint(x) >> 16);
+            x -= __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+          }
+        }
+      }
+    }
   }
 }
 
@@ -477,19 +522,20 @@ struct Tile {
 #pragma unroll
       for (int o = 0; o < S::NO; ++o)
         if (has(o) && (S::MT == 2 || c < 8))
-          put4<Op::kA, false>(X() + (c + S::PR) * l.sx + f0(o), l.px,
+          put4<Op, kPlain>(X() + (c + S::PR) * l.sx + f0(o), l.px,
                               ep[0][o]);
     }
   }
 
-  // The stage input into LDS.
+  // The stage input (or a stage's cotangent) into LDS.
+  template <PutKind KIND = kInput>
   __device__ __forceinline__ void put_input(const Vec& Y) {
 #pragma unroll
     for (int o = 0; o < S::NO; ++o)
 #pragma unroll
       for (int m = 0; m < S::OM; ++m)
         if (has(o) && (!S::CNF || S::MT == 2 || c < 8))
-          put4<Op::kA, true>(X() + (m * 16 + c) * l.sx + f0(o), l.px,
+          put4<Op, KIND>(X() + (m * 16 + c) * l.sx + f0(o), l.px,
                              Y[m][o]);
   }
 
@@ -577,9 +623,9 @@ struct Tile {
             if (!prim) a[i] = fmaf(-ap, ap, 1.f) * keep[i];
           }
         }
-        put4<Op::kA, false>(out + (m * 16 + c) * S::SA + f, S::PA, a);
+        put4<Op, kPlain>(out + (m * 16 + c) * S::SA + f, S::PA, a);
         if (S::CNF && S::MT == 2)
-          put4<Op::kA, false>(out + (16 + c) * S::SA + f, S::PA, ta);
+          put4<Op, kPlain>(out + (16 + c) * S::SA + f, S::PA, ta);
         if (act != nullptr) {
           // activations of primal rows, pre-activation tangents of tangents
           const int g = r0 + (prim ? m * 16 + c : c - 8);
