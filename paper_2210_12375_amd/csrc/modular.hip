@@ -1962,15 +1962,22 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
       }
 }
 
-template <typename R, int WM, int WN>
+// WALK: fewer workgroups than the nblk tiles and splits walk them (how many run
+// at a time changes no sum).  A kernel of its own: the loop costs registers,
+// which few workgroups have and a full chip has not (1024 instances of
+// 65->256->256->64 in BF16 922 -> 1016 us with the loop in all launches).
+template <typename R, int WM, int WN, bool WALK>
 __global__ __launch_bounds__(256) void grad_gemm_mfma(
-    const R* Tin, const R* Tg, long K, int M, int N, int S, R* slots, long P,
-    long off, long sin, long sg, long sslot) {
+    const R* Tin, const R* Tg, long K, int M, int N, int S, int nblk,
+    R* slots, long P, long off, long sin, long sg, long sslot) {
   __shared__ R As[16 * (32 * WM + 16)];
   __shared__ R Bs[16 * (32 * WN + 16)];
-  grad_gemm_tile<R, WM, WN>(blockIdx.x, Tin + blockIdx.y * sin,
-                         Tg + blockIdx.y * sg, K, M, N, S,
-                         slots + blockIdx.y * sslot, P, off, As, Bs);
+  int b = blockIdx.x;
+  do {
+    grad_gemm_tile<R, WM, WN>(b, Tin + blockIdx.y * sin,
+                              Tg + blockIdx.y * sg, K, M, N, S,
+                              slots + blockIdx.y * sslot, P, off, As, Bs);
+  } while (WALK && (b += gridDim.x) < nblk);
 }
 
 // Tile shapes of the matrix-core gradient products.
@@ -1989,35 +1996,39 @@ struct GemmGroup {
   R* slots;
 };
 
-template <typename R>
+template <typename R, bool WALK>
 __global__ __launch_bounds__(256) void grad_gemm_group(GemmGroup<R> g) {
   __shared__ R As[16 * (128 + 16)];
   __shared__ R Bs[16 * (128 + 16)];
-  int b = blockIdx.x, j = 0;
-  while (j < 2 && b >= g.nblk[j]) b -= g.nblk[j++];
-  const R *Tin = g.Tin[j], *Tg = g.Tg[j];
-  const int M = g.M[j], N = g.N[j], S = g.S[j];
-  switch (g.shape[j]) {
-    case kG14:
-      grad_gemm_tile<R, 1, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
-                              g.off[j], As, Bs);
-      break;
-    case kG41:
-      grad_gemm_tile<R, 4, 1>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
-                              g.off[j], As, Bs);
-      break;
-    case kG42:
-      grad_gemm_tile<R, 4, 2>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
-                              g.off[j], As, Bs);
-      break;
-    case kG34:
-      grad_gemm_tile<R, 3, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
-                              g.off[j], As, Bs);
-      break;
-    default:
-      grad_gemm_tile<R, 4, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
-                              g.off[j], As, Bs);
-  }
+  const int all = g.nblk[0] + g.nblk[1] + g.nblk[2];
+  int x = blockIdx.x;
+  do {
+    int b = x, j = 0;
+    while (j < 2 && b >= g.nblk[j]) b -= g.nblk[j++];
+    const R *Tin = g.Tin[j], *Tg = g.Tg[j];
+    const int M = g.M[j], N = g.N[j], S = g.S[j];
+    switch (g.shape[j]) {
+      case kG14:
+        grad_gemm_tile<R, 1, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                                g.off[j], As, Bs);
+        break;
+      case kG41:
+        grad_gemm_tile<R, 4, 1>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                                g.off[j], As, Bs);
+        break;
+      case kG42:
+        grad_gemm_tile<R, 4, 2>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                                g.off[j], As, Bs);
+        break;
+      case kG34:
+        grad_gemm_tile<R, 3, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                                g.off[j], As, Bs);
+        break;
+      default:
+        grad_gemm_tile<R, 4, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+                                g.off[j], As, Bs);
+    }
+  } while (WALK && (x += gridDim.x) < all);
 }
 
 // Large layers (both sides >= 256, long tapes): 256 x 256 tiles of C over
@@ -2318,14 +2329,27 @@ void grad_gemm_bf16(
 constexpr long kMinSplit = 64;
 // Products that run beside the cotangent chain of a small batch leave it the
 // compute units it needs (its workgroups fill one each, and one that finds
-// none waits for a product's to end): wgs is the most workgroups they take.
+// none waits for a product's to end): wgs is the most workgroups they take,
+// each of which then walks several splits of 384 rows.  (Fewer, longer splits
+// have the same speed and longer FP32 sums: gradients of a 500-instance CNF
+// of width 512 came out 2.9 times further from 64 bits in splits of 2333.
+// Splits of 256, one and a third a workgroup: 980 us against 920 below.)
 // 1024 instances of 65->256->256->64, step VJP 58 us beside 256, 48 beside 128.
 constexpr int kAllWgs = 1 << 20;
-inline int k_splits(long K, long tiles, long round, int S) {
+inline int k_splits(long K, long tiles, long round, int S,
+                    int wgs = kAllWgs) {
+  const long fill = std::min(wgs, 256);
   const long most = std::max<long>(
-      K / 256, std::min<long>(K / kMinSplit, (256 + tiles - 1) / tiles));
+      K / (wgs < kAllWgs ? 384 : 256),
+      std::min<long>(K / kMinSplit, (fill + tiles - 1) / tiles));
   return (int)std::max<long>(
       1, std::min<long>(std::min<long>(most, S), (round + tiles - 1) / tiles));
+}
+
+// Workgroups for `items` tiles and splits: about wgs, each with as many.
+inline int walkers(long items, int wgs) {
+  const long rounds = std::max<long>(1, (items + wgs / 2) / wgs);
+  return (int)((items + rounds - 1) / rounds);
 }
 
 // Launch shape of a parameter-gradient product C[M, N] = sum over K tape
@@ -2353,13 +2377,13 @@ inline GemmPlan plan_grad_gemm(bool f32, long K, int M, int N, int S,
   else if (M <= 96 && N > 64) wm = 3, p.shape = kG34;
   const int tm = 32 * wm, tn = 32 * wn;
   p.tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
-  p.splits = k_splits(K, (long)p.tiles * nb, std::min(wgs, 2048), S);
+  p.splits = k_splits(K, (long)p.tiles * nb, 2048, S, wgs);
   p.big = f32 && M - 1 >= 256 && N >= 256 && K * nb >= 65536;
   if (p.big) {
     // weight rows on 256 x 256 tiles; the bias row is the last input
     // feature and rides with the first row of tiles
     p.tb = ((M - 1 + 255) / 256) * ((N + 255) / 256);
-    p.sb = k_splits(K, (long)p.tb * nb, std::min(wgs, 1024), S);
+    p.sb = k_splits(K, (long)p.tb * nb, 1024, S);
   }
   return p;
 }
@@ -2420,8 +2444,8 @@ hipError_t launch_grad_gemm(const R* Tin, const R* Tg, long K, int M, int N,
   if (nb < 1 || (nb > 1 && sslot < (long)S * P)) return hipErrorInvalidValue;
   const bool f32 = std::is_same<R, float>::value;
   const GemmPlan pl = plan_grad_gemm(f32, K, M, N, S, nb, wgs);
-  const dim3 g(pl.tiles * pl.splits, nb), blk(256);
-  const int splits = pl.splits;
+  const int splits = pl.splits, nblk = pl.tiles * splits;
+  const dim3 g(walkers(nblk, wgs), nb), blk(256);
   if constexpr (std::is_same<R, float>::value) {
     if (bf16 && nb == 1 && M - 1 >= 256 && N >= 256) {
       const BgPlan p = plan_bf16(K, M, N, S, wgs);
@@ -2439,27 +2463,21 @@ hipError_t launch_grad_gemm(const R* Tin, const R* Tg, long K, int M, int N,
       return hipGetLastError();
     }
   }
+#define BODE_GEMM(wm, wn)                                                   \
+  do {                                                                      \
+    auto k = (int)g.x < nblk ? grad_gemm_mfma<R, wm, wn, true>              \
+                             : grad_gemm_mfma<R, wm, wn, false>;            \
+    hipLaunchKernelGGL(k, g, blk, 0, s, Tin, Tg, K, M, N, splits, nblk,     \
+                       slots, P, off, sin, sg, sslot);                      \
+  } while (0)
   switch (pl.shape) {
-    case kG14:
-      hipLaunchKernelGGL((grad_gemm_mfma<R, 1, 4>), g, blk, 0, s, Tin, Tg, K,
-                         M, N, splits, slots, P, off, sin, sg, sslot);
-      break;
-    case kG41:
-      hipLaunchKernelGGL((grad_gemm_mfma<R, 4, 1>), g, blk, 0, s, Tin, Tg, K,
-                         M, N, splits, slots, P, off, sin, sg, sslot);
-      break;
-    case kG42:
-      hipLaunchKernelGGL((grad_gemm_mfma<R, 4, 2>), g, blk, 0, s, Tin, Tg, K,
-                         M, N, splits, slots, P, off, sin, sg, sslot);
-      break;
-    case kG34:
-      hipLaunchKernelGGL((grad_gemm_mfma<R, 3, 4>), g, blk, 0, s, Tin, Tg, K,
-                         M, N, splits, slots, P, off, sin, sg, sslot);
-      break;
-    default:
-      hipLaunchKernelGGL((grad_gemm_mfma<R, 4, 4>), g, blk, 0, s, Tin, Tg, K,
-                         M, N, splits, slots, P, off, sin, sg, sslot);
+    case kG14: BODE_GEMM(1, 4); break;
+    case kG41: BODE_GEMM(4, 1); break;
+    case kG42: BODE_GEMM(4, 2); break;
+    case kG34: BODE_GEMM(3, 4); break;
+    default: BODE_GEMM(4, 4);
   }
+#undef BODE_GEMM
   return hipGetLastError();
 }
 
@@ -2496,8 +2514,10 @@ hipError_t launch_grad_gemm3(const R* const Tin[3], const R* const Tg[3],
       g.K = K;
       g.P = P;
       g.slots = slots;
-      hipLaunchKernelGGL(grad_gemm_group<R>, dim3((unsigned)nblk), dim3(256), 0,
-                         s, g);
+      const int wg = walkers(nblk, wgs);
+      auto k = wg < nblk ? grad_gemm_group<R, true>
+                         : grad_gemm_group<R, false>;
+      hipLaunchKernelGGL(k, dim3(wg), dim3(256), 0, s, g);
       return hipGetLastError();
     }
   }
@@ -2518,14 +2538,19 @@ __global__ void reduce_slots(const R* slots, int G, long P, R* out) {
   out += blockIdx.y * P;
   R acc = R(0);
   int g = 0;
-  for (; g + 16 <= G; g += 16) {  // 16 loads in flight, added in order
+  for (; g + 16 <= G; g += 16) {  // 16 loads in flight, added in pairs
     R v[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) v[j] = slots[(long)(g + j) * P + p];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) acc += v[j];
+    for (int w = 8; w > 0; w /= 2)
+#pragma unroll
+      for (int j = 0; j < w; ++j) v[j] += v[j + w];
+    acc += v[0];
   }
-  for (; g < G; ++g) acc += slots[(long)g * P + p];
+  R rest = R(0);
+  for (; g < G; ++g) rest += slots[(long)g * P + p];
+  acc += rest;
   out[p] = acc;
 }
 
