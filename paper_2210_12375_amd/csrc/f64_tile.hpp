@@ -32,54 +32,12 @@
 #include "common.hpp"
 #include "f64_mfma.hpp"
 #include "f64_shape.hpp"
+#include "tanh.hpp"
 
 namespace bode {
 namespace f64t {
 
 typedef double d2 __attribute__((ext_vector_type(2)));
-
-// tanh with e^z - 1, z = -2 |x|, as a sum of two doubles and the quotient
-// -(e^z - 1) / (2 + (e^z - 1)) corrected by its residual: mean error 0.25
-// ulp, largest 0.8 (2^20 points in each of nine ranges of |x| from 1e-300 to
-// 700; the library's: 0.25 to 0.28, largest 0.86).  89 instructions for
-// its 187, in the two hidden layers of every evaluation: 1000 instances of
-// 65->256->256->64 568 -> 521 us, 250 instances of
-// 33->128->128->32 with adjoint 1.03 -> 0.99 ms.  The polynomial (e^r - 1 - r) / r^2 on
-// |r| <= ln 2 / 2 interpolates at Chebyshev nodes, to 2^-60 of e^r - 1.
-__device__ __forceinline__ double tanh64(double x) {
-#pragma clang fp contract(off)
-  const double y = fabs(x), z = -2.0 * y;
-  const double k = rint(z * 1.4426950408889634);
-  const double r1 = fma(-k, 0.6931471526622772, z);  // exact
-  const double r = fma(-k, 2.7897668087737545e-08, r1);
-  const double rl = fma(-k, 2.7897668087737545e-08, r1 - r);
-  double q = 2.091468696808688e-09;
-  q = fma(q, r, 2.5105217004720745e-08);
-  q = fma(q, r, 2.75572736431103e-07);
-  q = fma(q, r, 2.7557255400206422e-06);
-  q = fma(q, r, 2.4801587325547743e-05);
-  q = fma(q, r, 0.00019841269874820627);
-  q = fma(q, r, 0.0013888888888883748);
-  q = fma(q, r, 0.008333333333326136);
-  q = fma(q, r, 0.04166666666666667);
-  q = fma(q, r, 0.1666666666666667);
-  q = fma(q, r, 0.5);
-  // e^r - 1 = p + pl, e^z - 1 = m + ml
-  const double w = (r * r) * q, p = r + w;
-  const double pl = ((r - p) + w) + rl;
-  const double s = ldexp(1.0, int(k)), s1 = s - 1.0, b = s * p, m = s1 + b;
-  const double bb = m - s1;
-  const double ml = 
-      fma(s, pl, (s1 - (m - bb)) + (b - bb)) + (s - (s1 + 1.0));
-  const double d = 2.0 + m, dl = (m - (d - 2.0)) + ml;
-  double v = __builtin_amdgcn_rcp(d);
-  v = fma(fma(-d, v, 1.0), v, v);
-  v = fma(fma(-d, v, 1.0), v, v);
-  double t = -m * v;
-  t = fma(fma(-dl, t, fma(-d, t, -m) - ml), v, t);
-  t = y > 40.0 ? 1.0 : t;  // (infinities too)
-  return copysign(t, x);
-}
 
 // C[MT][NT] += A (LDS, 4 MT rows) x column tiles nb0 .. nb0 + NT - 1 of the
 // packed layer at W (nk k blocks, nn column tiles; tiles past the last are
@@ -201,7 +159,7 @@ __device__ __forceinline__ void field_tile(const F64Args& a, int r0,
         for (int g = 0; g < MP; ++g) {
           const int r = g * 4 + i4, row = r0 + r;
           // (padding columns stay zero: 0 x inf would spread NaN)
-          const double v = n < H ? tanh64(acc[g][t]) : 0.0;
+          const double v = n < H ? tanh64<HwMath>(acc[g][t]) : 0.0;
           dst[r * d.SA + n] = v;
           if (CNF)
             dst[(PR + r) * d.SA + n] =
