@@ -34,6 +34,7 @@
 #include "common.hpp"
 #include "mlp_mfma.hpp"
 #include "mlp_mfma_tile.hpp"
+#include "tanh.hpp"
 
 namespace bode {
 namespace ntile {
@@ -60,20 +61,6 @@ struct Bf1 {
   __device__ static __forceinline__ float tanh(float x) { return fast_tanh(x); }
 };
 
-// tanh to about one ulp (FP32 mode): x + x^3 q(x^2) below 0.6 (q fitted at
-// Chebyshev nodes, relative error 8e-8 in float arithmetic), 1 - 2 e /
-// (1 + e) with e = exp(-2 |x|) above.
-__device__ __forceinline__ float close_tanh(float x) {
-  const float ax = fabsf(x), z = x * x;
-  const float e = __builtin_amdgcn_exp2f(ax * -2.8853900817779268f);
-  const float big = fmaf(-2.f * e, __builtin_amdgcn_rcpf(1.f + e), 1.f);
-  float q = fmaf(-0.006276387721300125f, z, 0.021116213873028755f);
-  q = fmaf(q, z, -0.053875137120485306f);
-  q = fmaf(q, z, 0.13332924246788025f);
-  q = fmaf(q, z, -0.3333333134651184f);
-  return ax < 0.6f ? fmaf(x, z * q, x) : copysignf(big, x);
-}
-
 // FP32 mode: weights and activations both as three terms.  Of the nine
 // products the six largest are issued; terms are rounded to nearest, so the
 // three dropped are at most about 2^-26 of a product together, below the
@@ -93,7 +80,7 @@ struct Bf6 {
   static constexpr int kTerm[kN][2] = {{0, 2}, {2, 0}, {1, 1},
                                        {0, 1}, {1, 0}, {0, 0}};
   __device__ static __forceinline__ float tanh(float x) {
-    return close_tanh(x);
+    return tanh32<HwMath>(x);
   }
 };
 

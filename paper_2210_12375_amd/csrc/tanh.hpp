@@ -1,6 +1,6 @@
-// tanh of the FP64 neural fields.  M supplies what the hardware does in one
-// instruction (approximate reciprocal, exponent), so that the arithmetic around
-// it can be checked on a host.
+// tanh of the neural fields, in float and double.  M supplies what the
+// hardware does in one instruction (approximate reciprocal and exp2), so that
+// the arithmetic around it can be checked on a host.
 #pragma once
 
 #include <cmath>
@@ -13,6 +13,29 @@
 #endif
 
 namespace bode {
+
+// About one ulp: x + x^3 q(x^2) below 1 (q interpolates at Chebyshev nodes,
+// the last bits of its first two coefficients chosen for the least mean error
+// in float arithmetic), 1 - 2 e / (1 + e) with e = exp(-2 |x|) above.
+// Measured over 2^18 points in each of 17 ranges from 0.01 to 100: at most
+// 1.24 ulp, rms 0.29 to 0.31 below 1 and 0.36 above, falling to 0.29.  The
+// library's tanhf, which the padded widths had: 1.40, 0.29 to 0.43 and 0.34;
+// with a polynomial of degree 4 to 0.6 only: 1.61 and 0.46 (1 % of the time of
+// 40,000 instances of 65->256->256->64 less).
+template <class M>
+BODE_TANH float tanh32(float x) {
+  const float ax = std::fabs(x), z = x * x;
+  const float e = M::exp2(ax * -2.8853900817779268f);
+  const float big = std::fma(-2.f * e, M::rcp(1.f + e), 1.f);
+  float q = std::fma(0.00014279318565968424f, z, -0.0009235008619725704f);
+  q = std::fma(q, z, 0.0032068034633994102f);
+  q = std::fma(q, z, -0.008697847835719585f);
+  q = std::fma(q, z, 0.021829549223184586f);
+  q = std::fma(q, z, -0.05396341532468796f);
+  q = std::fma(q, z, 0.13333308696746826f);
+  q = std::fma(q, z, -0.3333333134651184f);
+  return std::copysign(ax < 1.f ? std::fma(ax, z * q, ax) : big, x);
+}
 
 // e^z - 1, z = -2 |x|, as a sum of two doubles and the quotient
 // -(e^z - 1) / (2 + (e^z - 1)) corrected by its residual: mean error 0.25
@@ -62,8 +85,14 @@ BODE_TANH double tanh64(double x) {
 
 #if defined(__HIPCC__)
 struct HwMath {
+  __device__ static __forceinline__ float rcp(float x) {
+    return __builtin_amdgcn_rcpf(x);
+  }
   __device__ static __forceinline__ double rcp(double x) {
     return __builtin_amdgcn_rcp(x);
+  }
+  __device__ static __forceinline__ float exp2(float x) {
+    return __builtin_amdgcn_exp2f(x);
   }
   __device__ static __forceinline__ double exp2i(int k) {
     return ldexp(1.0, k);
