@@ -1876,7 +1876,10 @@ struct Mm4<double> {
 
 // Workgroup bx of the product (tile_split); As, Bs: LDS of at least
 // 16 (32 WM + 16) and 16 (32 WN + 16) values.
-template <typename R, int WM, int WN>
+// FEW > 0: a launch of few workgroups.  FEW == 2: their registers have room for
+// the sums of every 128 rows beside their total (FP32 mode; a BF16 field's
+// gradients are further off by its weights' rounding, and it costs 1 %).
+template <typename R, int WM, int WN, int FEW>
 __device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
                                                const R* Tg, long K, int M,
                                                int N, int S, R* slots, long P,
@@ -1896,11 +1899,16 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * 16 * WM, wn = (wave & 1) * 16 * WN;
   const int lr = lane & 15, lk = lane >> 4;
-  V acc[WM][WN];
+  constexpr bool kTot = FEW == 2;
+  V acc[WM][WN], tot[kTot ? WM : 1][kTot ? WN : 1];
 #pragma unroll
   for (int i = 0; i < WM; ++i)
 #pragma unroll
-    for (int j = 0; j < WN; ++j) acc[i][j] = V{R(0), R(0), R(0), R(0)};
+    for (int j = 0; j < WN; ++j) {
+      acc[i][j] = V{R(0), R(0), R(0), R(0)};
+      if constexpr (kTot) tot[i][j] = acc[i][j];
+    }
+  int rows = 0;
   // the next 16 tape rows are loaded into registers while the current ones
   // are multiplied
   R ra[NA], rb[NB];
@@ -1947,6 +1955,17 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
         for (int j = 0; j < WN; ++j)
           acc[i][j] = Mm4<R>::mul(a[i], b[j], acc[i][j]);
     }
+    if constexpr (kTot)
+      if ((rows += TK) == 128 || kk + TK >= k1) {
+        rows = 0;
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+          for (int j = 0; j < WN; ++j) {
+            tot[i][j] += acc[i][j];
+            acc[i][j] = V{R(0), R(0), R(0), R(0)};
+          }
+      }
     __syncthreads();
   }
   R* slot = slots + (long)split * P + off;
@@ -1958,15 +1977,16 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
       for (int v = 0; v < 4; ++v) {
         const int m = m0 + wm + i * 16 + Mm4<R>::row(lk, v);
         const int n = n0 + wn + j * 16 + lr;
-        if (m < M && n < N) slot[(long)m * N + n] += acc[i][j][v];
+        const R sum = kTot ? tot[kTot ? i : 0][kTot ? j : 0][v] : acc[i][j][v];
+        if (m < M && n < N) slot[(long)m * N + n] += sum;
       }
 }
 
-// WALK: fewer workgroups than the nblk tiles and splits walk them (how many run
-// at a time changes no sum).  A kernel of its own: the loop costs registers,
-// which few workgroups have and a full chip has not (1024 instances of
-// 65->256->256->64 in BF16 922 -> 1016 us with the loop in all launches).
-template <typename R, int WM, int WN, bool WALK>
+// FEW > 0: the workgroups, fewer than the nblk tiles and splits, walk them (how
+// many run at a time changes no sum).  A kernel of its own: the loop costs
+// registers, which few workgroups have and a full chip has not (1024 instances
+// of 65->256->256->64 in BF16 922 -> 1016 us with the loop in all launches).
+template <typename R, int WM, int WN, int FEW>
 __global__ __launch_bounds__(256) void grad_gemm_mfma(
     const R* Tin, const R* Tg, long K, int M, int N, int S, int nblk,
     R* slots, long P, long off, long sin, long sg, long sslot) {
@@ -1974,10 +1994,10 @@ __global__ __launch_bounds__(256) void grad_gemm_mfma(
   __shared__ R Bs[16 * (32 * WN + 16)];
   int b = blockIdx.x;
   do {
-    grad_gemm_tile<R, WM, WN>(b, Tin + blockIdx.y * sin,
+    grad_gemm_tile<R, WM, WN, FEW>(b, Tin + blockIdx.y * sin,
                               Tg + blockIdx.y * sg, K, M, N, S,
                               slots + blockIdx.y * sslot, P, off, As, Bs);
-  } while (WALK && (b += gridDim.x) < nblk);
+  } while (FEW > 0 && (b += gridDim.x) < nblk);
 }
 
 // Tile shapes of the matrix-core gradient products.
@@ -1996,7 +2016,7 @@ struct GemmGroup {
   R* slots;
 };
 
-template <typename R, bool WALK>
+template <typename R, int FEW>
 __global__ __launch_bounds__(256) void grad_gemm_group(GemmGroup<R> g) {
   __shared__ R As[16 * (128 + 16)];
   __shared__ R Bs[16 * (128 + 16)];
@@ -2009,26 +2029,26 @@ __global__ __launch_bounds__(256) void grad_gemm_group(GemmGroup<R> g) {
     const int M = g.M[j], N = g.N[j], S = g.S[j];
     switch (g.shape[j]) {
       case kG14:
-        grad_gemm_tile<R, 1, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+        grad_gemm_tile<R, 1, 4, FEW>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
                                 g.off[j], As, Bs);
         break;
       case kG41:
-        grad_gemm_tile<R, 4, 1>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+        grad_gemm_tile<R, 4, 1, FEW>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
                                 g.off[j], As, Bs);
         break;
       case kG42:
-        grad_gemm_tile<R, 4, 2>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+        grad_gemm_tile<R, 4, 2, FEW>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
                                 g.off[j], As, Bs);
         break;
       case kG34:
-        grad_gemm_tile<R, 3, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+        grad_gemm_tile<R, 3, 4, FEW>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
                                 g.off[j], As, Bs);
         break;
       default:
-        grad_gemm_tile<R, 4, 4>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
+        grad_gemm_tile<R, 4, 4, FEW>(b, Tin, Tg, g.K, M, N, S, g.slots, g.P,
                                 g.off[j], As, Bs);
     }
-  } while (WALK && (x += gridDim.x) < all);
+  } while (FEW > 0 && (x += gridDim.x) < all);
 }
 
 // Large layers (both sides >= 256, long tapes): 256 x 256 tiles of C over
@@ -2431,6 +2451,14 @@ hipError_t launch_bf16(const BgPlan& p, const float* Tin, const float* Tg,
   return hipGetLastError();
 }
 
+// The form of a launch limited to wgs workgroups (grad_gemm_tile's FEW).
+template <typename R>
+constexpr int kFew2 = std::is_same<R, float>::value ? 2 : 1;
+template <typename R>
+int few_of(bool bf16, int wgs) {
+  return wgs >= kAllWgs ? 0 : bf16 ? 1 : kFew2<R>;
+}
+
 // nb > 1: nb products of the same shape in one launch (grid y), product j
 // reading Tin + j sin and Tg + j sg and adding into its own S slots at
 // slots + j sslot (sslot >= S P).  bf16: BF16 mode, whose products with
@@ -2463,13 +2491,15 @@ hipError_t launch_grad_gemm(const R* Tin, const R* Tg, long K, int M, int N,
       return hipGetLastError();
     }
   }
-#define BODE_GEMM(wm, wn)                                                   \
-  do {                                                                      \
-    auto k = (int)g.x < nblk ? grad_gemm_mfma<R, wm, wn, true>              \
-                             : grad_gemm_mfma<R, wm, wn, false>;            \
-    hipLaunchKernelGGL(k, g, blk, 0, s, Tin, Tg, K, M, N, splits, nblk,     \
-                       slots, P, off, sin, sg, sslot);                      \
+#define BODE_GEMM(wm, wn)                                                  \
+  do {                                                                     \
+    auto k = few == 2   ? grad_gemm_mfma<R, wm, wn, kFew2<R>>              \
+             : few == 1 ? grad_gemm_mfma<R, wm, wn, 1>                     \
+                        : grad_gemm_mfma<R, wm, wn, 0>;                    \
+    hipLaunchKernelGGL(k, g, blk, 0, s, Tin, Tg, K, M, N, splits, nblk,    \
+                       slots, P, off, sin, sg, sslot);                     \
   } while (0)
+  const int few = few_of<R>(bf16, wgs);
   switch (pl.shape) {
     case kG14: BODE_GEMM(1, 4); break;
     case kG41: BODE_GEMM(4, 1); break;
@@ -2515,8 +2545,10 @@ hipError_t launch_grad_gemm3(const R* const Tin[3], const R* const Tg[3],
       g.P = P;
       g.slots = slots;
       const int wg = walkers(nblk, wgs);
-      auto k = wg < nblk ? grad_gemm_group<R, true>
-                         : grad_gemm_group<R, false>;
+      const int few = few_of<R>(bf16, wgs);
+      auto k = few == 2   ? grad_gemm_group<R, kFew2<R>>
+               : few == 1 ? grad_gemm_group<R, 1>
+                          : grad_gemm_group<R, 0>;
       hipLaunchKernelGGL(k, dim3(wg), dim3(256), 0, s, g);
       return hipGetLastError();
     }
