@@ -134,6 +134,25 @@ __device__ __forceinline__ double keep(uint32_t m, double x) {
   return pick(m, x, 0.0);
 }
 
+// Matrix-core sums, before ordinary instructions read them.  A product's result
+// may be read only some wait states after its issue (19 for the longest,
+// v_mfma_f64_16x16x4_f64); the compiler counts those inside a block, but was
+// seen to miss them where a branch leads straight from the last product of a
+// loop to the first read, so they are spent here.  The empty statements tie
+// every accumulator to its place.
+template <typename V, int M, int N>
+__device__ __forceinline__ void settle(V (&acc)[M][N]) {
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+v"(acc[i][j]));
+  asm volatile("s_nop 15\n\ts_nop 3");
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+v"(acc[i][j]));
+}
+
 template <typename R>
 __device__ __forceinline__ R quiet_nan();
 template <>

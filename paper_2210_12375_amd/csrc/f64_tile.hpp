@@ -81,6 +81,7 @@ __device__ __forceinline__ void gemm(double (&acc)[MT][NT], const double* A,
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  settle(acc);
 }
 
 // The field for the tile of instances starting at r0.  KL: the stage values

@@ -1958,6 +1958,7 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
     if constexpr (kTot)
       if ((rows += TK) == 128 || kk + TK >= k1) {
         rows = 0;
+        settle(acc);
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
@@ -1968,6 +1969,7 @@ __device__ __forceinline__ void grad_gemm_tile(int bx, const R* Tin,
       }
     __syncthreads();
   }
+  settle(acc);
   R* slot = slots + (long)split * P + off;
 #pragma unroll
   for (int i = 0; i < WM; ++i)
@@ -2127,6 +2129,7 @@ __global__ __launch_bounds__(512) void grad_gemm_big(
     }
     __syncthreads();
   }
+  settle(acc);
   float* slot = slots + (long)split * P + off;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -2320,6 +2323,7 @@ void grad_gemm_bf16(
     if (more) stage(bg_mem + cur * kBuf, kk + kBgK);
     __syncthreads();
   }
+  settle(acc);
   float* slot = slots + (long)split * P + off;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
