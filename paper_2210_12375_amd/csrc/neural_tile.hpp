@@ -719,10 +719,13 @@ struct Tile {
   }
 };
 
+// Four floats of a caller's array, which may lie at any float.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
 // Elements f .. f + 3 of a row of `lim` (zero beyond).
 __device__ __forceinline__ f32x4 row4(const float* p, int f, int lim,
                                       bool vec) {
-  if (vec && f + 3 < lim) return *reinterpret_cast<const f32x4*>(p + f);
+  if (vec && f + 3 < lim) return *reinterpret_cast<const f32x4u*>(p + f);
   f32x4 v{};
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] = f + i < lim ? p[f + i] : 0.f;
@@ -731,7 +734,7 @@ __device__ __forceinline__ f32x4 row4(const float* p, int f, int lim,
 __device__ __forceinline__ void put_row4(float* p, int f, int lim, bool vec,
                                          f32x4 v) {
   if (vec && f + 3 < lim) {
-    *reinterpret_cast<f32x4*>(p + f) = v;
+    *reinterpret_cast<f32x4u*>(p + f) = v;
     return;
   }
 #pragma unroll
