@@ -5,9 +5,10 @@
 // Candidates:
 //  - analytic fields (the persistent per-lane solver): threads per workgroup
 //    {64, 128, 256} x lanes launched per kind of instance {B, B/2, B/4};
-//  - neural fields: wavefronts per 16-row tile {4, 8} (the default for the
-//    width first) for the matrix-core kernels, and for the per-stage path
-//    rounds per captured graph / running-count read-back {4, 8, 16}.
+//  - neural fields: one or two 16-row tiles per workgroup (the values 8 and
+//    4) where the matrix-core kernels are built for both, and for the
+//    per-stage path rounds per captured graph / running-count read-back
+//    {4, 8, 16}.
 // Every candidate computes the same result bit for bit (the shapes change
 // which lane or wavefront does a piece of work, never the order of any
 // sum), so the search only picks the fastest.
@@ -77,9 +78,9 @@ int autotune(const bode_config* cfg, const bode_problem* p, void* workspace,
     const bool mfma = neural_fused(cfg->precision, din, cfg->mlp_hidden);
     const bool fused = mfma && !cfg->keep_dense;
     std::vector<int> waves = {0};
-    if (mfma && cfg->mlp_hidden > 64) {
+    if (mfma && row_tile_choice(cfg->precision == BODE_FP32, din,
+                                cfg->mlp_hidden))
       waves = {8, 4};
-    }
     std::vector<int> rounds = {0};
     if (!fused) rounds = {8, 4, 16};
     for (int w : waves)

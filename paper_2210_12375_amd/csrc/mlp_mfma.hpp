@@ -44,6 +44,13 @@ std::string mfma_supported(int din, int H);
 // widths hold the shape, at any width in between (padding a 50-wide layer to
 // 64 costs nothing beside the FMA kernel it replaces: 11.7 -> 0.78 ms).
 bool neural_fused(int precision, int din, int H);
+// Whether its kernels are built for one and for two row tiles a workgroup:
+// eight wavefronts, none of which has two tiles of the output layer, and in
+// BF16 with the weights resident below width 512 (fwd_op in neural_fwd.inc).
+inline bool row_tile_choice(bool f32, int din, int H) {
+  const int h = mfma_pad_h(H);
+  return h > 64 && mfma_pad_din(din) <= (f32 || h == 512 ? 128 : 64);
+}
 
 hipError_t mfma_pack_weights(const MfmaWeights& w, int din, int H,
                              const float* W1, const float* b1, const float* W2,
@@ -71,7 +78,7 @@ struct MfmaArgs {
   // whose tangent rows follow), layer 1 then layer 2 of each row; the
   // activation on primal rows, the pre-activation tangent on tangent rows.
   float* act_out;
-  // wavefronts per 16-row tile: 4 or 8 (0: the default for the width)
+  // 16-row tiles per workgroup: 8 asks for one, 4 for two (0: the default)
   int waves;
 };
 

@@ -58,7 +58,7 @@ struct Tune {
   int block = 0;      // analytic: threads per workgroup of the solve kernel
   int lanes_vdp = 0;  // analytic: lanes launched for each kind of instance
   int lanes_lin = 0;
-  int waves = 0;      // neural: wavefronts per 16-row tile (4 or 8)
+  int waves = 0;      // neural: 8: one 16-row tile a workgroup, 4: two
   int rounds = 0;     // neural per-stage path: rounds per graph / read-back
 };
 // set_tune also rewrites the tune cache file; set_tune_candidate only

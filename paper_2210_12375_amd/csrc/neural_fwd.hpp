@@ -44,8 +44,8 @@ struct FwdSteps {
   float* act[7];
 };
 
-// waves: wavefronts per 16-row tile, 8 (a tile per workgroup) or 4 (two), 0
-// for the default.  Both give bitwise the same results.
+// waves: 8 for one 16-row tile per workgroup, 4 for two, 0 for the default
+// (where both are built: row_tile_choice).  Both give bitwise the same results.
 hipError_t fwd_solve(const Mod<float>& m, const MfmaWeights& w,
                      const TableauArgs& t, int budget, int waves,
                      hipStream_t s);
