@@ -68,9 +68,13 @@ struct Bf1 {
 // per 1024 products of a tile, six BF16 products of 8 k each 3; measured
 // against it (40,000 instances of 65->256->256->64) 4.57 -> 2.94 ms, and
 // against plain FMA where the widths are no multiples of 16 (300 instances
-// of 7->50->50->6 with their adjoint) 11.7 -> 0.78 ms.  Relative error
-// against 64-bit solves of the same steps, 20 draws: final states 0.7-1.0e-7
-// (1.0-1.8e-7 before), state gradients 1.8-2.3e-7 (2.0-3.6e-7).
+// of 7->50->50->6 with their adjoint) 11.7 -> 0.78 ms.  Relative l2 errors
+// beside those of the kernels replaced, at three regular and five padded
+// widths (50 to 256 units, 200 to 1200 instances, 8 draws), against 64 bits on
+// the same steps, in 2^-24: state gradients 2.5-3.0 -> 2.5-2.6 (padded 2.5-2.9
+// -> 2.5-2.6), parameter gradients, worst layer, 4.5-4.7 -> 3.0-3.3 (3.6-4.9 ->
+// 2.7-3.8); of 16 shapes' final states against 64-bit solves, 0.37 to 0.98 of
+// the former error.
 struct Bf6 {
   // the five small products accumulate apart from hi x hi, so a sum over k is
   // rounded at its own size once per 32 k, not six times (in one accumulator
@@ -210,7 +214,6 @@ struct Net {
   const uint16_t* w;
   unsigned wbytes;
   const float* fvec;
-  const float* eps;
 };
 
 __host__ __device__ inline int k_split(int nn3, int wv, int nkh) {
