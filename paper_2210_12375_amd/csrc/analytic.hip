@@ -363,7 +363,11 @@ __device__ __forceinline__ bool attempt(const AnalyticArgs<R>& a,
   fac = fmin(pick(macc, K.hi, R(INFINITY)), fac);
   fac = fmin(pick(macc, L.cap, R(INFINITY)), fac);
 
-  if (accept && __builtin_expect(L.tw[0] <= tnew, 0)) {
+  // (the FP64 linear kernel's eight-time window: laid out as unlikely, the
+  // outputs spilled 270 scalars into the step, 700 instances with 256 times
+  // 3050 us against 1850; with the short window 985 against 1006)
+  const bool dense = accept && L.tw[0] <= tnew;
+  if (N == 2 || TW == 2 ? __builtin_expect(dense, 0) : dense) {
     // Dense output at this instance's own evaluation times in (t, t_new]
     // (Horner in theta, then the stage combination).
     do {
@@ -1095,10 +1099,17 @@ constexpr int kWindowMinE = 64;
 // wavefronts on a unit slow each other, at 512 by a third): 256 FP32
 // instances with 200 times 183 us in four wavefronts, 134 in 256; 4096 with
 // 256 times 303 in 64, 284 in 256, but 64 times 132 and 133; FP64, 4096 with
-// 256 times, 331 and 365.
+// 256 times, 331 and 365.  With few times there is little to wait for, and
+// every wavefront fetches its instances and the kernel's code by itself: small
+// batches are spread from 8 times on, linear FP64 ones from 48.  64 linear FP64 instances of a
+// sweep, none / 32 / 64 times, together 780 / 960 / 1120 us, spread 990 / 1000 /
+// 1100; 64 linear FP32 375 / 540 / 620 and 460 / 475 / 505, level at 8; Van der
+// Pol FP64 none / 16 1250 / 1388 and 1300 / 1290, FP32 none / 8 500 / 580 and
+// 520 / 530.
 constexpr int kSpread = 256, kSpreadE = 128;
-inline int lanes_per_wave(int lanes, int E, bool f32) {
-  if (lanes > kSpread && !(f32 && E >= kSpreadE)) return 64;
+inline int lanes_per_wave(int lanes, int E, bool f32, bool vdp) {
+  const int few_e = vdp ? 8 : f32 ? 8 : 48;
+  if (lanes > kSpread ? !(f32 && E >= kSpreadE) : E < few_e) return 64;
   return std::min(64, std::max(1, (lanes + kSpread - 1) / kSpread));
 }
 
@@ -1134,7 +1145,8 @@ hipError_t launch_analytic_solve(const AnalyticArgs<R>& a, int method,
   const int width = kind == kKindVdp ? kLanes<R, VdpField<R>> : 1;
   if (width == 2) block += block & 1;  // (both lanes of a pair)
   const int per_wave = std::min(
-      64 / width, lanes_per_wave(lanes, a.E, std::is_same<R, float>::value));
+      64 / width, lanes_per_wave(lanes, a.E, std::is_same<R, float>::value,
+                                 kind == kKindVdp));
   const long waves = (lanes + per_wave - 1) / per_wave;
   const int grid = (int)((waves * 64 + block - 1) / block);
   if (grid == 0) return hipSuccess;
